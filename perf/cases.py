@@ -104,6 +104,8 @@ def draw(rng):
         c["kT"] = 0.0  # the deterministic method
     c["steps"] = max(1, min(50, int(rng.uniform(0.2, 1.0) * 2 ** 27 / (nx * ny * nz)), rng.randint(1, 50)))
     c["stats_every"] = rng.choice([0, 0, 0, 1, 5])
+    if c["kT"] == 0.0:
+        c["stats_every"] = 0  # the statistics are of the fluctuations
     c["out"] = "populations" if storage == "f32" and nx * ny * nz < 2 ** 22 else "moments"
     return c
 
@@ -171,7 +173,7 @@ def prepare(case, seed):
         lat.step(c["steps"])
     elif c["kind"] == "restart":
         lat.step(c["steps"])
-        s["to"] = rf.Lattice((c["nx"], c["ny"], c["nz"]), **_params(c, seed))
+        s["params"] = _params(c, seed)
     elif c["stats_every"]:
         lat.stats_config(c["stats_every"])
     return s
@@ -201,7 +203,7 @@ def run(state):
             spectra[f] = (sums / np.maximum(counts, 1) / samples).astype(np.float32)
         return {"spectra": spectra, "counts": counts}
     if c["kind"] == "restart":
-        to = state["to"]
+        to = rf.Lattice(lat.dims, **state["params"])  # the resumed program's own lattice
         to.set_populations(lat.populations())
         to.t = lat.t
         to.step(2)
