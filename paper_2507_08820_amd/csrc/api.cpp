@@ -165,6 +165,8 @@ GatherArgs gather_args(const rflbm_lattice* L, const rflbm_params& p, int64_t t)
   g.plane_pitch = L->L.plane_pitch / storage_bytes(p.storage);
   g.by_log = L->L.by_log;
   g.bz_log = L->L.bz_log;
+  g.div_x = make_fastdiv(static_cast<uint32_t>(p.nx));
+  g.div_y = make_fastdiv(static_cast<uint32_t>(p.ny));
   g.odd = static_cast<uint32_t>(t & 1);
   g.rho0 = p.rho0;
   sigma_of(p, g.sigma, g.inv_sigma);

@@ -161,6 +161,7 @@ struct GatherArgs {
   uint64_t zin_pitch;     // elements from one x-row block to the next in z inside a brick (Zi)
   uint64_t plane_pitch;   // elements from one brick row (Bz z planes) to the next (P)
   uint32_t by_log, bz_log;  // brick shape, as in StepArgs
+  FastDiv div_x, div_y;   // division by nx and by ny
   uint32_t odd;           // parity of the current step count
   double rho0;
   float sigma[4];
