@@ -8,6 +8,8 @@
 // count f_i(x) sits in slot A[i][x], at an odd one in A[26 - i][x - c_i].
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "d3q27.hpp"
 #include "kernels.hpp"
 #include "philox.hpp"
@@ -47,21 +49,63 @@ __device__ __forceinline__ uint64_t slot_index(int i, NodeXYZ p, const GatherArg
                        wrap_add(p.z, -cz, g.nz), g);
 }
 
-template <int S>
-__global__ void get_pop_kernel(const GatherArgs g, double* dst) {
+// Node n < 2^32 -> (x, y, z) with two magic divisions.
+__device__ __forceinline__ NodeXYZ coords32(uint32_t n, const GatherArgs& g) {
+  NodeXYZ c;
+  const uint32_t r = fast_div(n, g.div_x);
+  c.x = n - r * g.nx;
+  c.z = fast_div(r, g.div_y);
+  c.y = r - c.z * g.ny;
+  return c;
+}
+
+// Element indices of the 27 slots of one node: the row blocks (and x positions)
+// they lie in are found once, a slot is then one of them plus its population row.
+template <bool ODD>
+struct Slots {
+  uint64_t row[9];  // row block of (y - c_y, z - c_z), at c_y + 1 + 3 (c_z + 1); even: row[4] only
+  uint32_t xs[3];   // x - c_x, at c_x + 1
+  uint32_t pitch;
+  __device__ __forceinline__ Slots(NodeXYZ p, const GatherArgs& g) : pitch(static_cast<uint32_t>(g.pop_pitch)) {
+    if constexpr (ODD) {
+#pragma unroll
+      for (int c = -1; c <= 1; ++c) xs[c + 1] = wrap_add(p.x, -c, g.nx);
+#pragma unroll
+      for (int q = 0; q < 9; ++q)
+        row[q] = element_index(0, 0, wrap_add(p.y, 1 - q % 3, g.ny), wrap_add(p.z, 1 - q / 3, g.nz), g);
+    } else {
+      row[4] = element_index(0, p.x, p.y, p.z, g);
+    }
+  }
+  __device__ __forceinline__ uint64_t operator()(int i) const {
+    if constexpr (ODD) return row[i / 3] + (xs[i % 3] + static_cast<uint32_t>(kQ - 1 - i) * pitch);
+    else return row[4] + static_cast<uint32_t>(i) * pitch;
+  }
+};
+
+// f(x, t) of every node, FP64 planar.  Bound by memory: 27 stored words in, 27
+// FP64 values out a node.  One thread per node, whose 27 loads are in flight
+// together; the outputs are streamed (non-temporal), since they are twice to
+// four times the populations and only push those out of the caches.  192^3
+// FP32 0.51 -> 0.43 ms, 256^3 FP16 1.24 -> 0.83 ms (6.6 TB/s copy rate: 0.35
+// and 0.69); one population per block instead of 27 per thread took 0.49 and
+// 1.09 ms.
+template <int S, bool ODD>
+__global__ void __launch_bounds__(256) get_pop_kernel(const GatherArgs g, double* __restrict__ dst) {
   using C = Codec<S>;
   using T = typename C::T;
-  const uint64_t N = static_cast<uint64_t>(g.nx) * g.ny * g.nz;
+  const uint32_t N = g.nx * g.ny * g.nz;
   const T* pop = static_cast<const T*>(g.pop);
-  for (uint64_t n = blockIdx.x * static_cast<uint64_t>(blockDim.x) + threadIdx.x; n < N;
-       n += static_cast<uint64_t>(gridDim.x) * blockDim.x) {
-    const NodeXYZ p = coords(n, g.nx, g.ny);
+  const uint64_t n64 = blockIdx.x * static_cast<uint64_t>(256) + threadIdx.x;
+  if (n64 >= N) return;
+  const uint32_t n = static_cast<uint32_t>(n64);
+  const Slots<ODD> slot(coords32(n, g), g);
 #pragma unroll
-    for (int i = 0; i < kQ; ++i) {
-      const int cls = speed_class(i);
-      const float d = C::decode(pop[slot_index(i, p, g)], g.sigma[cls]);
-      dst[i * N + n] = class_weight(cls) * g.rho0 + static_cast<double>(d);
-    }
+  for (int i = 0; i < kQ; ++i) {
+    const int cls = speed_class(i);
+    const float d = C::decode(pop[slot(i)], g.sigma[cls]);
+    const double v = class_weight(cls) * g.rho0 + static_cast<double>(d);
+    __builtin_nontemporal_store(v, dst + static_cast<uint64_t>(i) * N + n);
   }
 }
 
@@ -137,40 +181,6 @@ __global__ void init_eq_kernel(const GatherArgs g, const double* rho, const doub
     }
   }
 }
-
-// Node n < 2^32 -> (x, y, z) with two magic divisions.
-__device__ __forceinline__ NodeXYZ coords32(uint32_t n, const GatherArgs& g) {
-  NodeXYZ c;
-  const uint32_t r = fast_div(n, g.div_x);
-  c.x = n - r * g.nx;
-  c.z = fast_div(r, g.div_y);
-  c.y = r - c.z * g.ny;
-  return c;
-}
-
-// Element indices of the 27 slots of one node: the row blocks (and x positions)
-// they lie in are found once, a slot is then one of them plus its population row.
-template <bool ODD>
-struct Slots {
-  uint64_t row[9];  // row block of (y - c_y, z - c_z), at c_y + 1 + 3 (c_z + 1); even: row[4] only
-  uint32_t xs[3];   // x - c_x, at c_x + 1
-  uint32_t pitch;
-  __device__ __forceinline__ Slots(NodeXYZ p, const GatherArgs& g) : pitch(static_cast<uint32_t>(g.pop_pitch)) {
-    if constexpr (ODD) {
-#pragma unroll
-      for (int c = -1; c <= 1; ++c) xs[c + 1] = wrap_add(p.x, -c, g.nx);
-#pragma unroll
-      for (int q = 0; q < 9; ++q)
-        row[q] = element_index(0, 0, wrap_add(p.y, 1 - q % 3, g.ny), wrap_add(p.z, 1 - q / 3, g.nz), g);
-    } else {
-      row[4] = element_index(0, p.x, p.y, p.z, g);
-    }
-  }
-  __device__ __forceinline__ uint64_t operator()(int i) const {
-    if constexpr (ODD) return row[i / 3] + (xs[i % 3] + static_cast<uint32_t>(kQ - 1 - i) * pitch);
-    else return row[4] + static_cast<uint32_t>(i) * pitch;
-  }
-};
 
 // cos and sin of 2 pi a / 65536, a in 0 .. 65535, in FP64: a = 16384 q + r with
 // |r| <= 8192 exactly, then the Taylor series on |theta| <= pi / 4 (the first
@@ -300,35 +310,45 @@ __global__ void __launch_bounds__(256) init_thermal_kernel(const GatherArgs g, c
 
 // Moment fields of the nodes n0 .. n0 + count - 1: field c of node n0 + k goes
 // to dst[c * pitch + k].
-template <int S>
-__global__ void moments_kernel(const GatherArgs g, uint32_t mask, uint64_t n0, uint64_t count,
-                               uint64_t pitch, float* dst) {
+// NT: populations read past the caches (more than the memory-side cache holds,
+// and each cache line read by one wave only, so not at odd step counts): 192^3
+// FP32 0.197 -> 0.173 ms, 256^3 FP16 0.295 -> 0.253 ms; a box that fits the
+// cache loses by it (130 x 101 x 97 BF16 0.023 -> 0.030 ms).
+template <int S, bool ODD, bool NT>
+__global__ void __launch_bounds__(256) moments_kernel(const GatherArgs g, uint32_t mask, uint64_t n0, uint64_t count,
+                                                      uint64_t pitch, float* __restrict__ dst) {
   using C = Codec<S>;
   using T = typename C::T;
   const T* pop = static_cast<const T*>(g.pop);
-  for (uint64_t k = blockIdx.x * static_cast<uint64_t>(blockDim.x) + threadIdx.x; k < count;
-       k += static_cast<uint64_t>(gridDim.x) * blockDim.x) {
-    const NodeXYZ p = coords(n0 + k, g.nx, g.ny);
-    float v[kQ];
+  const uint64_t k = blockIdx.x * static_cast<uint64_t>(256) + threadIdx.x;
+  if (k >= count) return;
+  const Slots<ODD> slot(coords32(static_cast<uint32_t>(n0 + k), g), g);
+  float v[kQ];
 #pragma unroll
-    for (int i = 0; i < kQ; ++i) v[i] = C::decode(pop[slot_index(i, p, g)], g.sigma[speed_class(i)]);
-    forward27(v);
-    float* out = dst;
-    if (mask & 1u) {
-      out[k] = static_cast<float>(g.rho0 + static_cast<double>(v[0]));
-      out += pitch;
-    }
-    if (mask & 2u) {
-      out[k] = v[1];
-      out[pitch + k] = v[3];
-      out[2 * pitch + k] = v[9];
-      out += 3 * pitch;
-    }
-    if (mask & 4u) {
-      const int slots[6] = {mode_slot(4), mode_slot(5), mode_slot(6), mode_slot(7), mode_slot(8), mode_slot(9)};
+  for (int i = 0; i < kQ; ++i) {
+    const T q = NT ? __builtin_nontemporal_load(pop + slot(i)) : pop[slot(i)];
+    v[i] = C::decode(q, g.sigma[speed_class(i)]);
+  }
+  forward27(v);
+  float* out = dst;
+  auto put = [&](uint64_t at, float q) {
+    if constexpr (NT) __builtin_nontemporal_store(q, out + at);
+    else out[at] = q;
+  };
+  if (mask & 1u) {
+    put(k, static_cast<float>(g.rho0 + static_cast<double>(v[0])));
+    out += pitch;
+  }
+  if (mask & 2u) {
+    put(k, v[1]);
+    put(pitch + k, v[3]);
+    put(2 * pitch + k, v[9]);
+    out += 3 * pitch;
+  }
+  if (mask & 4u) {
+    const int slots[6] = {mode_slot(4), mode_slot(5), mode_slot(6), mode_slot(7), mode_slot(8), mode_slot(9)};
 #pragma unroll
-      for (int c = 0; c < 6; ++c) out[c * pitch + k] = v[slots[c]];
-    }
+    for (int c = 0; c < 6; ++c) put(c * pitch + k, v[slots[c]]);
   }
 }
 
@@ -450,6 +470,9 @@ __global__ void plane_restore_kernel(const GatherArgs g, int dst, const W* tmp, 
 }
 
 
+// Memory-side cache of an MI355X (Infinity Cache): reads of less may stay in it.
+constexpr uint64_t kCacheBytes = 256ull << 20;
+
 uint32_t grid_for(uint64_t work, uint32_t block) {
   const uint64_t g = (work + block - 1) / block;
   return static_cast<uint32_t>(g < 65536 ? (g == 0 ? 1 : g) : 65536);
@@ -482,10 +505,26 @@ hipError_t swap_parity_words(const GatherArgs& g, W* tmp, hipStream_t s) {
     }                                                                                       \
   } while (0)
 
+// Calls f(integral_constant<int, S>) for the storage type; the launch error, if any.
+template <class F>
+hipError_t with_storage(int storage, F f) {
+  switch (storage) {
+    case kF32: f(std::integral_constant<int, kF32>{}); break;
+    case kF16: f(std::integral_constant<int, kF16>{}); break;
+    case kBF16: f(std::integral_constant<int, kBF16>{}); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
 hipError_t launch_get_populations(int storage, const GatherArgs& g, double* dst, hipStream_t s) {
   const uint64_t N = static_cast<uint64_t>(g.nx) * g.ny * g.nz;
-  RFLBM_DISPATCH_STORAGE(storage, get_pop_kernel, dim3(grid_for(N, 256)), dim3(256), s, g, dst);
-  return hipGetLastError();
+  const dim3 grid(static_cast<uint32_t>((N + 255) / 256)), block(256);
+  return with_storage(storage, [&](auto st) {
+    constexpr int S = decltype(st)::value;
+    if (g.odd) hipLaunchKernelGGL((get_pop_kernel<S, true>), grid, block, 0, s, g, dst);
+    else hipLaunchKernelGGL((get_pop_kernel<S, false>), grid, block, 0, s, g, dst);
+  });
 }
 
 hipError_t launch_get_populations_at(int storage, const GatherArgs& g, const uint32_t* nodes, uint32_t count,
@@ -513,28 +552,13 @@ hipError_t launch_init_thermal(int storage, const GatherArgs& g, const double* r
                                hipStream_t s) {
   const uint64_t N = static_cast<uint64_t>(g.nx) * g.ny * g.nz;
   const dim3 grid(static_cast<uint32_t>((N + 255) / 256)), block(256);
-#define RFLBM_THERMAL_P(S, R)                                                                                \
-  if (g.odd)                                                                                                 \
-    hipLaunchKernelGGL((init_thermal_kernel<S, R, true>), grid, block, 0, s, g, rho, u, key0, key1, sid, kT); \
-  else                                                                                                       \
-    hipLaunchKernelGGL((init_thermal_kernel<S, R, false>), grid, block, 0, s, g, rho, u, key0, key1, sid, kT);
-#define RFLBM_THERMAL(R)                           \
-  switch (storage) {                               \
-    case kF32: RFLBM_THERMAL_P(kF32, R) break;     \
-    case kF16: RFLBM_THERMAL_P(kF16, R) break;     \
-    case kBF16: RFLBM_THERMAL_P(kBF16, R) break;   \
-    default: return hipErrorInvalidValue;          \
-  }
-  if (rounds == 10) {
-    RFLBM_THERMAL(10)
-  } else if (rounds == 7) {
-    RFLBM_THERMAL(7)
-  } else {
-    return hipErrorInvalidValue;
-  }
-#undef RFLBM_THERMAL
-#undef RFLBM_THERMAL_P
-  return hipGetLastError();
+  if (rounds != 7 && rounds != 10) return hipErrorInvalidValue;
+  return with_storage(storage, [&](auto st) {
+    constexpr int S = decltype(st)::value;
+    const auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, s, g, rho, u, key0, key1, sid, kT); };
+    if (rounds == 7) go(g.odd ? init_thermal_kernel<S, 7, true> : init_thermal_kernel<S, 7, false>);
+    else go(g.odd ? init_thermal_kernel<S, 10, true> : init_thermal_kernel<S, 10, false>);
+  });
 }
 
 hipError_t launch_get_moments(int storage, const GatherArgs& g, uint32_t mask, float* dst,
@@ -546,9 +570,15 @@ hipError_t launch_get_moments(int storage, const GatherArgs& g, uint32_t mask, f
 hipError_t launch_get_moments_range(int storage, const GatherArgs& g, uint32_t mask, uint64_t n0,
                                     uint64_t count, float* dst, uint64_t pitch, hipStream_t s) {
   if (count == 0) return hipSuccess;
-  RFLBM_DISPATCH_STORAGE(storage, moments_kernel, dim3(grid_for(count, 256)), dim3(256), s, g, mask, n0,
-                         count, pitch, dst);
-  return hipGetLastError();
+  const dim3 grid(static_cast<uint32_t>((count + 255) / 256)), block(256);
+  const uint64_t pop_bytes = static_cast<uint64_t>(kQ) * g.nx * g.ny * g.nz * storage_bytes(storage);
+  const bool nt = !g.odd && pop_bytes > kCacheBytes;
+  return with_storage(storage, [&](auto st) {
+    constexpr int S = decltype(st)::value;
+    const auto kernel = g.odd ? moments_kernel<S, true, false>
+                              : (nt ? moments_kernel<S, false, true> : moments_kernel<S, false, false>);
+    hipLaunchKernelGGL(kernel, grid, block, 0, s, g, mask, n0, count, pitch, dst);
+  });
 }
 
 hipError_t launch_reencode(int storage, const GatherArgs& from, const GatherArgs& to, hipStream_t s) {
