@@ -172,10 +172,8 @@ int64_t rflbm_step_count(const rflbm_lattice* lat);
 /* Sets the time t of Eq. eq:streaming (checkpoint restart: set_populations + set_step_count resumes a run
  * bit for bit, since the noise depends only on (seed, n, t, stream_id)).  A
  * change of parity moves the stored state to the other AA layout in place and
- * bit for bit, with a temporary device buffer of one population plane
- * (nx ny nz stored words), freed before the call returns.  ENOMEM (no room for
- * that buffer) leaves the lattice unchanged; after an EHIP during the move the
- * stored populations are undefined until they are set again. */
+ * bit for bit, in stream order and without scratch memory; after an EHIP from
+ * the move the stored populations are undefined until they are set again. */
 rflbm_status rflbm_set_step_count(rflbm_lattice* lat, int64_t t);
 
 /* Reads the pre-collision populations f_i(x, t) of Eq. eq:streaming (the
@@ -325,9 +323,8 @@ rflbm_status rflbm_batch_step_separate(rflbm_batch* b, int64_t nsteps);
 /* Waits; EUNSTABLE if any replica's instability flag is set. */
 rflbm_status rflbm_batch_sync(rflbm_batch* b);
 int64_t rflbm_batch_step_count(const rflbm_batch* b);
-/* Sets t for every replica (checkpoint restart of a batch).  A change of parity
- * takes one temporary population plane of the largest replica, allocated
- * before any replica moves: ENOMEM leaves the batch unchanged. */
+/* Sets t for every replica (checkpoint restart of a batch), as
+ * rflbm_set_step_count does for a lattice. */
 rflbm_status rflbm_batch_set_step_count(rflbm_batch* b, int64_t t);
 /* The ensemble statistics of rflbm_stats_config (Sec. III, equilibration
  * ratios) for every replica of the batch: sampled by the batched step on every

@@ -20,9 +20,8 @@
 namespace rflbm {
 hipError_t launch_sk_bin(const void* spec, uint32_t nx, uint32_t ny, uint32_t nz, uint32_t nshells,
                          double* shell_sum, unsigned long long* shell_count, hipStream_t s);
-// Moves the stored state to the other AA parity in place, as raw stored words;
-// tmp holds one population plane (nx ny nz words of the storage type).
-hipError_t launch_swap_parity(int storage, const GatherArgs& g, void* tmp, hipStream_t s);
+// Moves the stored state to the other AA parity in place, as raw stored words.
+hipError_t launch_swap_parity(int storage, const GatherArgs& g, hipStream_t s);
 }
 
 using namespace rflbm;
@@ -365,31 +364,13 @@ rflbm_status lattice_steps(rflbm_lattice* L, int64_t nsteps) {
   return RFLBM_OK;
 }
 
-size_t parity_scratch_bytes(const rflbm_lattice* L) { return nodes(L) * storage_bytes(L->p.storage); }
-
-rflbm_status lattice_set_step_count_with(rflbm_lattice* L, int64_t t, void* tmp) {
-  if (t < 0) return fail(RFLBM_EINVAL, "step count must be >= 0");
-  if ((t & 1) != (L->t & 1)) {
-    // the storage layout depends on the parity: move the state to the new one,
-    // in place and bit for bit, through one population plane of scratch
-    hipError_t e = launch_swap_parity(L->p.storage, gather_args(L, L->p, L->t), tmp, L->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(L->stream);
-    if (e != hipSuccess) return hip_fail(RFLBM_EHIP, "re-layout", e);
-  }
-  L->t = t;
-  return RFLBM_OK;
-}
-
 rflbm_status lattice_set_step_count(rflbm_lattice* L, int64_t t) {
   if (t < 0) return fail(RFLBM_EINVAL, "step count must be >= 0");
-  void* tmp = nullptr;
-  if ((t & 1) != (L->t & 1)) {
-    if (const hipError_t m = hipMalloc(&tmp, parity_scratch_bytes(L)); m != hipSuccess)
-      return hip_fail(RFLBM_ENOMEM, "re-layout scratch", m);
-  }
-  const rflbm_status st = lattice_set_step_count_with(L, t, tmp);
-  if (tmp) (void)hipFree(tmp);
-  return st;
+  // the storage layout depends on the parity: move the state to the new one
+  if ((t & 1) != (L->t & 1))
+    RFLBM_HIP(launch_swap_parity(L->p.storage, gather_args(L, L->p, L->t), L->stream));
+  L->t = t;
+  return RFLBM_OK;
 }
 
 }  // namespace rflbm

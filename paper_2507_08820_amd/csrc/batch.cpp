@@ -11,7 +11,6 @@
 // step counter read by the kernel, and the per-tile statistics partials.
 #include <hip/hip_runtime.h>
 
-#include <algorithm>
 #include <cstdio>
 #include <cstring>
 #include <fstream>
@@ -417,20 +416,8 @@ rflbm_status rflbm_batch_step_separate(rflbm_batch* b, int64_t nsteps) {
 rflbm_status rflbm_batch_set_step_count(rflbm_batch* b, int64_t t) {
   if (rflbm_status s = check_batch(b)) return s;
   if (t < 0) return fail(RFLBM_EINVAL, "step count must be >= 0");
-  // one scratch plane for the largest replica, taken before any replica moves,
-  // so that running out of memory leaves the whole batch unchanged
-  void* tmp = nullptr;
-  if ((t & 1) != (b->t & 1)) {
-    size_t bytes = 0;
-    for (rflbm_lattice* v : b->views) bytes = std::max(bytes, parity_scratch_bytes(v));
-    if (const hipError_t m = hipMalloc(&tmp, bytes); m != hipSuccess)
-      return hip_fail(RFLBM_ENOMEM, "re-layout scratch", m);
-  }
-  rflbm_status st = RFLBM_OK;
   for (rflbm_lattice* v : b->views)
-    if ((st = lattice_set_step_count_with(v, t, tmp)) != RFLBM_OK) break;
-  if (tmp) (void)hipFree(tmp);
-  if (st != RFLBM_OK) return st;
+    if (rflbm_status st = lattice_set_step_count(v, t)) return st;
   b->t = t;
   return RFLBM_OK;
 }
