@@ -608,9 +608,9 @@ def summarize_profiles(out_dir, dims=(512, 512, 512)):
         # of the tiled one
         if "copy_kernel" in name:
             return "copy"
-        if re.search(r"step_row_kernel<0, 7, \w+, false, true>|step_kernel<0, true, 7, false\b", name):
+        if re.search(r"step_row_kernel<0, 7, \w+, false, true\b|step_kernel<0, true, 7, false\b", name):
             return "odd"
-        if re.search(r"step_wave_kernel<0, 7\b|step_kernel<0, false, 7, false\b", name):
+        if re.search(r"step_wave_kernel<0, 7, \w+(?:>|, false)|step_kernel<0, false, 7, false\b", name):
             return "even"
         return None
 

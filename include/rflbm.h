@@ -265,14 +265,17 @@ rflbm_status rflbm_reset_sk(rflbm_lattice* lat);
 rflbm_status rflbm_set_launch(rflbm_lattice* lat, int32_t bx, int32_t xcd_remap);
 rflbm_status rflbm_get_launch(const rflbm_lattice* lat, int32_t* bx, int32_t* xcd_remap);
 
-/* Row-aligned blocks for the steps without statistics (the streaming of
- * Eq. eq:streaming in its two AA phases), used where the step is bound by
- * bandwidth: FP32 storage, or k_BT = 0.  When enabled and nx is a multiple of
- * 64, every even step runs one 64-node x-segment per block, and every odd step
- * one block per x-row (if nx <= 1024).  The shifts by c_x = +-1 then stay
- * inside a block (values move between lanes), and every load and store covers
- * whole aligned cache lines.  The 16-bit steps with noise are bound by
- * arithmetic and keep the tiled kernel.  Statistics steps, and all steps when
+/* Blocks that follow the x-rows (the streaming of Eq. eq:streaming in its two
+ * AA phases).  When enabled:
+ *   nx a multiple of 64: steps run in one-wave x-segments of 64 nodes, and
+ *     where the step is bound by bandwidth (FP32 storage, or k_BT = 0) odd
+ *     steps and statistics steps run one block per x-row (if nx <= 1024): the
+ *     shifts by c_x = +-1 then stay inside a block (values move between lanes),
+ *     and every load and store covers whole aligned cache lines;
+ *   other nx, populations below 4 GiB: every step runs in blocks of
+ *     consecutive nodes, row after row, so that rows need not fill waves.
+ * The 16-bit steps with noise keep the tiled kernel for large boxes with nx a
+ * multiple of 256, and for statistics; everything else, and all steps when
  * disabled, keep the tiled shape of rflbm_set_launch.  Results are bit for bit
  * the same either way.  Enabled by rflbm_create.  rflbm_get_row_blocks sets
  * *active to 1 when the next odd step runs in whole rows (it depends on

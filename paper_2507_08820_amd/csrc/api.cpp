@@ -197,6 +197,7 @@ StepArgs step_args(const rflbm_lattice* L) {
   const auto fd = [](uint32_t d) { return d >= 2 ? make_fastdiv(d) : FastDiv{0u, 1u}; };
   a.div_tiles_x = fd(a.tiles_x);
   a.div_tiles_y = fd(a.tiles_y);
+  a.div_nx = make_fastdiv(static_cast<uint32_t>(p.nx));
   a.div_ny = fd(static_cast<uint32_t>(p.ny));
   a.div_nyb = fd(static_cast<uint32_t>(p.ny) >> L->L.by_log);
   a.div_segs = fd(static_cast<uint32_t>(p.nx) / 64u);
@@ -254,14 +255,25 @@ void lattice_init(rflbm_lattice* L, const rflbm_params& p, uint8_t* buf, hipStre
 // or no noise (16-bit at 512^3 without noise: 2.46 ms per step against 2.74 ms
 // tiled).  The 16-bit steps with noise are bound by arithmetic: there the lane
 // moves and barriers of the whole-row odd step cost more than the aligned
-// accesses save (3.8 against 3.2 ms), and one-wave even steps between tiled
-// odd ones measured no faster than tiled ones (3.28-3.30 against 3.26-3.27 ms
-// per step), so those steps keep the tiled kernel.
+// accesses save (3.8 against 3.2 ms).
 static bool rows_pay(const rflbm_lattice* L) {
   return L->row_mode && (L->p.storage == RFLBM_F32 || L->p.kT == 0.0);
 }
 
 static bool odd_in_rows(const rflbm_lattice* L) { return rows_pay(L) && row_kernel_fits(L->p.nx); }
+
+// Steps without statistics in one-wave blocks (nx a multiple of 64): the even
+// ones of the lattices above, and the odd ones too long for a block; the 16-bit
+// steps with noise of both parities, whose rows then fill every wave (us per
+// step against the tiles of 128 or 256 nodes: 192^3 FP16 140 / 177, 320 x 96 x
+// 96 FP16 55 / 83, 192 x 128 x 128 BF16 57 / 75, 128^3 FP16 40.4 / 43.8), except
+// where tiles of 256 fit the rows and the box streams from memory (256^3 341 /
+// 336, 512^3 2773 / 2713).
+static bool in_waves(const rflbm_lattice* L, const StepArgs& a, bool odd) {
+  if (!L->row_mode || L->p.nx % 64 != 0) return false;
+  if (rows_pay(L)) return !odd || !row_kernel_fits(L->p.nx);
+  return !(L->p.nx % 256 == 0 && streams(a));
+}
 
 hipError_t lattice_clear(rflbm_lattice* L) {
   // populations (deviation 0 = rest at rho0), flag and accumulators
@@ -348,13 +360,16 @@ rflbm_status lattice_steps(rflbm_lattice* L, int64_t nsteps) {
     a.step = static_cast<uint32_t>(t & 0xffffffffu);
     const bool odd = (t & 1) != 0;
     uint32_t grid = L->launch.grid;  // blocks, hence statistics partials, of the kernel used
-    if ((odd || stats) && odd_in_rows(L)) {
+    if (L->row_mode && flat_kernel_fits(a)) {
+      RFLBM_HIP(launch_step_flat(L->p.storage, odd, rounds, stats, a, L->stream));
+      grid = flat_grid(a, stats);
+    } else if ((odd || stats) && odd_in_rows(L)) {
       // whole rows: odd steps, and even steps with statistics (one partial per
       // row; the one-wave even blocks would write one per wave)
       RFLBM_HIP(launch_step_row(L->p.storage, odd, rounds, stats, a, L->stream));
       grid = row_grid(L->p.ny, L->p.nz);
-    } else if (!odd && !stats && rows_pay(L) && L->p.nx % 64 == 0) {
-      RFLBM_HIP(launch_step_wave(L->p.storage, rounds, a, L->stream));
+    } else if (!stats && in_waves(L, a, odd)) {
+      RFLBM_HIP(launch_step_wave(L->p.storage, odd, rounds, a, L->stream));
     } else {
       RFLBM_HIP(launch_step(L->p.storage, odd, rounds, stats, a, L->launch, L->stream));
     }

@@ -50,6 +50,7 @@ struct StepArgs {
   uint32_t xcd_remap;    // 1: give each XCD a contiguous range of tiles
   FastDiv div_tiles_x;   // division by tiles_x (when tiles_x >= 2)
   FastDiv div_tiles_y;   // division by tiles_y (when tiles_y >= 2)
+  FastDiv div_nx;        // division by nx
   FastDiv div_ny;        // division by ny
   FastDiv div_nyb;       // division by ny / By (bricks along y)
   FastDiv div_segs;      // division by nx / 64 (when nx / 64 >= 2)
@@ -133,8 +134,8 @@ Launch make_launch(uint32_t nx, uint32_t ny, uint32_t nz, uint32_t bx, uint32_t 
 hipError_t launch_step(int storage, bool odd, int rounds, bool stats, const StepArgs& a,
                        const Launch& l, hipStream_t stream);
 
-// Even step without statistics in one-wave blocks (nx a multiple of 64).
-hipError_t launch_step_wave(int storage, int rounds, const StepArgs& a, hipStream_t stream);
+// Step without statistics in one-wave blocks (nx a multiple of 64).
+hipError_t launch_step_wave(int storage, bool odd, int rounds, const StepArgs& a, hipStream_t stream);
 
 // True when the odd step can run in whole-row blocks: nx a multiple of 64, at
 // most 64 kMaxRowWaves.
@@ -146,6 +147,19 @@ bool row_kernel_fits(uint32_t nx);
 hipError_t launch_step_row(int storage, bool odd, int rounds, bool stats, const StepArgs& a, hipStream_t stream);
 // Number of blocks of the whole-row odd step: ny nz rounded up to a multiple of 8.
 uint32_t row_grid(uint32_t ny, uint32_t nz);
+
+// Bytes from the first to past the last population row of the box.
+uint64_t pop_span(const StepArgs& a);
+// True when the box is too large for the memory-side cache to hold what a step
+// writes until the next step reads it.
+bool streams(const StepArgs& a);
+// True when a step can run in flat blocks: rows that do not fill whole waves, in
+// a box whose populations lie within 4 GiB.
+bool flat_kernel_fits(const StepArgs& a);
+// A step in blocks of consecutive nodes of the memory order, with stats one
+// partial per block of the flat_grid(a, stats) blocks.
+hipError_t launch_step_flat(int storage, bool odd, int rounds, bool stats, const StepArgs& a, hipStream_t stream);
+uint32_t flat_grid(const StepArgs& a, bool stats);
 
 // Deterministic reduction of the statistics partials into the accumulators.
 // scratch holds at least 2 * kNumStats * ceil(grid / 2048) doubles.

@@ -19,12 +19,13 @@
 //      values to their AA destination slots.
 // Everything between the 27 loads and the 27 stores stays in registers.
 //
-// The same body runs in four kernels: step_kernel (tiles of 256 nodes of one z
-// plane; every step shape, statistics included), step_wave_kernel (even steps
-// in one-wave x-segments), step_row_kernel (odd steps in whole x-rows, where
-// values move between lanes so that every access covers whole cache lines)
-// and batch_kernel (many boxes, persistent grid over tiles of consecutive
-// nodes).  The three one-box kernels take GEQ (every omega_g = 1) as a template
+// The same body runs in five kernels: step_kernel (tiles of 256 nodes of one z
+// plane; every step shape, statistics included), step_wave_kernel (steps in
+// one-wave x-segments), step_row_kernel (odd steps in whole x-rows, where
+// values move between lanes so that every access covers whole cache lines),
+// step_flat_kernel (consecutive nodes, for rows that do not fill waves) and
+// batch_kernel (many boxes, persistent grid over tiles of consecutive
+// nodes).  The four one-box kernels take GEQ (every omega_g = 1) as a template
 // parameter, and so does the batch kernel when every replica has it (else it
 // reads the setting per replica).
 #include <hip/hip_runtime.h>
@@ -39,44 +40,28 @@
 
 namespace rflbm {
 
+uint64_t pop_span(const StepArgs& a) { return static_cast<uint64_t>(a.nz >> a.bz_log) * a.plane_pitch; }
+
 namespace {
 
 constexpr int kBlock = 256;
 
-// Cache policy of the population accesses, per step parity.  The even step
-// reads and writes each node's own slots: nothing is reused, so its loads are
-// marked non-temporal.  The odd step reads and writes slots shifted by +-1 in
-// x; neighbouring waves share the boundary cache lines, so its accesses keep
-// the default policy and meet in L2.
-#ifndef RFLBM_EVEN_LOAD_NT
-#define RFLBM_EVEN_LOAD_NT 1
-#endif
-#ifndef RFLBM_EVEN_STORE_NT
-#define RFLBM_EVEN_STORE_NT 1
-#endif
-#ifndef RFLBM_ODD_LOAD_NT
-#define RFLBM_ODD_LOAD_NT 0
-#endif
-#ifndef RFLBM_ODD_STORE_NT
-#define RFLBM_ODD_STORE_NT 0
-#endif
 
-// In the odd step the 9 populations with c_x = 0 are shifted only by whole
-// rows, so their accesses do not share cache lines with neighbouring waves.
-#ifndef RFLBM_ODD_ALIGNED_NT
-#define RFLBM_ODD_ALIGNED_NT 0
-#endif
-
-// Cache policy of a population access of the tiled step; x_aligned (c_x = 0)
-// is a constant once the population loop is unrolled.
-template <bool ODD>
-__device__ __forceinline__ constexpr bool load_nt(bool x_aligned) {
-  return ODD ? (RFLBM_ODD_LOAD_NT || (x_aligned && RFLBM_ODD_ALIGNED_NT)) : RFLBM_EVEN_LOAD_NT;
-}
-template <bool ODD>
-__device__ __forceinline__ constexpr bool store_nt(bool x_aligned) {
-  return ODD ? (RFLBM_ODD_STORE_NT || (x_aligned && RFLBM_ODD_ALIGNED_NT == 1)) : RFLBM_EVEN_STORE_NT;
-}
+// Cache policy of the population accesses (NT in the kernels' scope: non-temporal).
+// Even steps, and odd steps in whole rows, read and write whole cache lines
+// that no other wave touches and that the step uses once; odd steps in other
+// blocks share the lines at the ends of their +-1-shifted ranges with
+// neighbouring waves and always keep the default policy, so that those meet in
+// L2.  Rows that are not aligned to lines keep it at both parities: with
+// non-temporal even steps 200^3 FP16 takes 244 us a step instead of 199, 300 x
+// 280 x 260 BF16 684 instead of 533.
+//
+// NT pays where the populations exceed what the 256 MiB memory-side cache still
+// holds of them from the last step: us per step with / without NT, FP32,
+// 216 MiB (128^3) 81 / 65, 270 MiB 103 / 84, 338 MiB 126 / 123, 506 MiB
+// 184 / 197, 1.7 GiB (256^3) 599 / 653; BF16 without noise 108 MiB (128^3)
+// 41 / 29, 324 MiB 134 / 137 (FP16), 864 MiB 303 / 328.
+constexpr uint64_t kStreamBytes = 320ull << 20;
 
 // Visiting order of the whole-row odd step: groups of 2 rows x 8 planes
 // (measured at 512^3: about 1 % faster than plain row order).
@@ -98,15 +83,6 @@ __device__ __forceinline__ void brick_row(uint32_t r, const StepArgs& a, uint32_
   y = (yb << a.by_log) + (inner & ((1u << a.by_log) - 1u));
   z = (zb << a.bz_log) + (inner >> a.by_log);
 }
-
-// Whole-row odd step: whole aligned cache lines that no other wave touches,
-// like those of the even step.
-#ifndef RFLBM_ROW_LOAD_NT
-#define RFLBM_ROW_LOAD_NT 1
-#endif
-#ifndef RFLBM_ROW_STORE_NT
-#define RFLBM_ROW_STORE_NT 1
-#endif
 
 // Population accesses are raw buffer instructions: a scalar resource (base
 // address, no range limit below 4 GiB), a 32-bit per-lane offset and a scalar
@@ -222,6 +198,27 @@ __device__ __forceinline__ void row_shift(uint32_t (&v)[kQ], uint32_t (*edge)[kM
   }
 }
 
+// Block sums of the staged statistics in FP64, fixed order (8 partial sums of 32
+// nodes per column), into column entry blockIdx.x of the partials.
+__device__ __forceinline__ void block_stats(const float (*stat_lds)[kBlock], uint32_t tid, double* partials) {
+  __shared__ double part[kNumStats][8];
+  __syncthreads();
+  if (tid < kNumStats * 8) {
+    const int c = tid >> 3, p = tid & 7;
+    double acc = 0.0;
+#pragma unroll 8
+    for (int e = 0; e < 32; ++e) acc += static_cast<double>(stat_lds[c][p * 32 + e]);
+    part[c][p] = acc;
+  }
+  __syncthreads();
+  if (tid < kNumStats) {
+    double acc = 0.0;
+#pragma unroll
+    for (int p = 0; p < 8; ++p) acc += part[tid][p];
+    partials[static_cast<size_t>(tid) * gridDim.x + blockIdx.x] = acc;
+  }
+}
+
 // One box: a block covers bx x by nodes of one z plane (blockDim = (bx, by));
 // blocks of one row (by = 1) take the rows in memory order, others plane by plane.
 template <int S, bool ODD, int ROUNDS, bool STATS, bool GEQ>
@@ -252,7 +249,7 @@ __global__ void __launch_bounds__(kBlock) step_kernel(const StepArgs a) {
     constexpr bool BUFFER_ACCESS = true;
     constexpr bool BRICKS = true;
     constexpr bool ROW_SHIFT = false;
-    constexpr bool GHOST_EQ = GEQ;
+    constexpr bool GHOST_EQ = GEQ, NT = true;
     [[maybe_unused]] uint32_t (*row_edge_in)[kMaxRowWaves] = nullptr;
     [[maybe_unused]] uint32_t (*row_edge_out)[kMaxRowWaves] = nullptr;
 #include "node_body.inc"
@@ -261,33 +258,56 @@ __global__ void __launch_bounds__(kBlock) step_kernel(const StepArgs a) {
     for (int c = 0; c < kNumStats; ++c) stat_lds[c][tid] = 0.0f;
   }
 
-  if constexpr (STATS) {
-    // fixed-order block reduction in FP64: 8 partial sums of 32 nodes per column
-    __shared__ double part[kNumStats][8];
-    __syncthreads();
-    if (tid < kNumStats * 8) {
-      const int c = tid >> 3, p = tid & 7;
-      double acc = 0.0;
-#pragma unroll 8
-      for (int e = 0; e < 32; ++e) acc += static_cast<double>(stat_lds[c][p * 32 + e]);
-      part[c][p] = acc;
-    }
-    __syncthreads();
-    if (tid < kNumStats) {
-      double acc = 0.0;
-#pragma unroll
-      for (int p = 0; p < 8; ++p) acc += part[tid][p];
-      a.partials[static_cast<size_t>(tid) * gridDim.x + blockIdx.x] = acc;
-    }
-  }
+  if constexpr (STATS) block_stats(stat_lds, tid, a.partials);
 }
 
-// Even step without statistics in one-wave blocks: block b covers the 64
+// One box whose rows do not fill whole waves, in blocks of consecutive nodes of
+// the memory order (row by row, brick_row), so that only the last block has
+// idle lanes; every population offset must fit 32 bits.  Bound as the tiled
+// step is, which left the lanes past each row's end idle (half of them at nx =
+// 130): us per step, tiled -> flat: 130 x 50 x 70 BF16 20.8 -> 12.8, FP32 26.7
+// -> 17.6; 96^3 FP32 36.4 -> 29.8, FP16 27.6 -> 21.0; 200^3 FP32 431 -> 341;
+// 300 x 280 x 260 BF16 795 -> 533.  Without statistics a block is one wave, so
+// that a small box spreads over more CUs: 17 x 19 x 23 FP32 4.4 us, in blocks of
+// 256 5.6, tiled 5.0; large boxes do not care.
+template <int S, bool ODD, int ROUNDS, bool STATS, bool GEQ>
+__global__ void __launch_bounds__(STATS ? kBlock : 64) step_flat_kernel(const StepArgs a) {
+  constexpr uint32_t BLOCK = STATS ? kBlock : 64;
+  uint32_t tile = blockIdx.x;
+  if (a.xcd_remap) tile = (tile & 7u) * (gridDim.x >> 3) + (tile >> 3);
+  const uint32_t tid = threadIdx.x;
+  const uint32_t m = tile * BLOCK + tid;
+  __shared__ float stat_lds[STATS ? kNumStats : 1][kBlock];
+  if (m < a.nx * a.ny * a.nz) {
+    const uint32_t row = fast_div(m, a.div_nx);
+    const uint32_t x = m - row * a.nx;
+    uint32_t y, z;
+    brick_row(row, a, y, z);
+    const uint32_t step = a.step;
+    constexpr bool STATS_WAVE = false;
+    [[maybe_unused]] float (*stat_wave)[kMaxRowWaves] = nullptr;
+    constexpr bool SMALL_BOX = true;
+    constexpr bool BUFFER_ACCESS = true;
+    constexpr bool BRICKS = true;
+    constexpr bool ROW_SHIFT = false;
+    constexpr bool GHOST_EQ = GEQ;
+    constexpr bool NT = false;
+    [[maybe_unused]] uint32_t (*row_edge_in)[kMaxRowWaves] = nullptr;
+    [[maybe_unused]] uint32_t (*row_edge_out)[kMaxRowWaves] = nullptr;
+#include "node_body.inc"
+  } else if constexpr (STATS) {
+#pragma unroll
+    for (int c = 0; c < kNumStats; ++c) stat_lds[c][tid] = 0.0f;
+  }
+  if constexpr (STATS) block_stats(stat_lds, tid, a.partials);
+}
+
+// Step without statistics in one-wave blocks: block b covers the 64
 // nodes x = 64 (b mod (nx / 64)) + lane of x-row b / (nx / 64) of the memory
 // order (brick_row; nx a multiple of 64).
-template <int S, int ROUNDS, bool GEQ>
+template <int S, int ROUNDS, bool GEQ, bool ODD, bool NT>
 __global__ void __launch_bounds__(64) step_wave_kernel(const StepArgs a) {
-  constexpr bool ODD = false, STATS = false, SMALL_BOX = false, ROW_SHIFT = false, BUFFER_ACCESS = true;
+  constexpr bool STATS = false, SMALL_BOX = false, ROW_SHIFT = false, BUFFER_ACCESS = true;
   constexpr bool BRICKS = true;
   constexpr bool GHOST_EQ = GEQ, STATS_WAVE = false;
   [[maybe_unused]] float (*stat_lds)[kBlock] = nullptr;
@@ -315,7 +335,7 @@ __global__ void __launch_bounds__(64) step_wave_kernel(const StepArgs a) {
 // nodes' statistics, and the block adds its waves' sums in FP64 (fixed order)
 // into one partial per block, as step_kernel does; the even step takes this
 // kernel only for statistics (one partial per row instead of one per wave).
-template <int S, int ROUNDS, bool GEQ, bool STATS, bool ODD>
+template <int S, int ROUNDS, bool GEQ, bool STATS, bool ODD, bool NT>
 __global__ void __launch_bounds__(kMaxRowWaves * 64) step_row_kernel(const StepArgs a) {
   constexpr bool SMALL_BOX = false, ROW_SHIFT = ODD, BUFFER_ACCESS = true, BRICKS = true;
   constexpr bool GHOST_EQ = GEQ, STATS_WAVE = true;
@@ -386,7 +406,7 @@ __global__ void __launch_bounds__(kBlock) batch_kernel(const BatchArgs b) {
   // buffer instructions measured faster for 16-bit storage, global ones for
   // FP32 (64 replicas of 32^3..96^3: 38.9 vs 36.6 and 24.6 vs 25.9 GLUPS)
   constexpr bool BUFFER_ACCESS = S != kF32;
-  constexpr bool ROW_SHIFT = false;
+  constexpr bool ROW_SHIFT = false, NT = true;
   [[maybe_unused]] uint32_t (*row_edge_in)[kMaxRowWaves] = nullptr;
   [[maybe_unused]] uint32_t (*row_edge_out)[kMaxRowWaves] = nullptr;
   __shared__ float stat_lds[STATS ? kNumStats : 1][kBlock];
@@ -512,16 +532,39 @@ hipError_t launch_t(const StepArgs& a, const Launch& l, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int S, int R, bool ST, bool ODD>
-void launch_row_g(const StepArgs& a, dim3 g, dim3 blk, hipStream_t s) {
-  if (a.ghost_eq) hipLaunchKernelGGL((step_row_kernel<S, R, true, ST, ODD>), g, blk, 0, s, a);
-  else hipLaunchKernelGGL((step_row_kernel<S, R, false, ST, ODD>), g, blk, 0, s, a);
+template <int S, bool ODD, int R, bool ST>
+void launch_flat_t(const StepArgs& a, uint32_t grid, hipStream_t s) {
+  if (a.ghost_eq) hipLaunchKernelGGL((step_flat_kernel<S, ODD, R, ST, true>), dim3(grid), dim3(ST ? kBlock : 64), 0, s, a);
+  else hipLaunchKernelGGL((step_flat_kernel<S, ODD, R, ST, false>), dim3(grid), dim3(ST ? kBlock : 64), 0, s, a);
 }
 
-template <int S, int R>
+template <int S, bool ODD, bool ST>
+hipError_t launch_flat_r(int rounds, const StepArgs& a, uint32_t grid, hipStream_t s) {
+  switch (rounds) {
+    case 0: launch_flat_t<S, ODD, 0, ST>(a, grid, s); break;
+    case 7: launch_flat_t<S, ODD, 7, ST>(a, grid, s); break;
+    case 10: launch_flat_t<S, ODD, 10, ST>(a, grid, s); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+template <int S>
+hipError_t launch_flat_s(bool odd, int rounds, bool stats, const StepArgs& a, uint32_t grid, hipStream_t s) {
+  if (odd) return stats ? launch_flat_r<S, true, true>(rounds, a, grid, s) : launch_flat_r<S, true, false>(rounds, a, grid, s);
+  return stats ? launch_flat_r<S, false, true>(rounds, a, grid, s) : launch_flat_r<S, false, false>(rounds, a, grid, s);
+}
+
+template <int S, int R, bool ST, bool ODD, bool NT>
+void launch_row_g(const StepArgs& a, dim3 g, dim3 blk, hipStream_t s) {
+  if (a.ghost_eq) hipLaunchKernelGGL((step_row_kernel<S, R, true, ST, ODD, NT>), g, blk, 0, s, a);
+  else hipLaunchKernelGGL((step_row_kernel<S, R, false, ST, ODD, NT>), g, blk, 0, s, a);
+}
+
+template <int S, int R, bool ODD, bool NT>
 void launch_wave_g(const StepArgs& a, dim3 g, hipStream_t s) {
-  if (a.ghost_eq) hipLaunchKernelGGL((step_wave_kernel<S, R, true>), g, dim3(64), 0, s, a);
-  else hipLaunchKernelGGL((step_wave_kernel<S, R, false>), g, dim3(64), 0, s, a);
+  if (a.ghost_eq) hipLaunchKernelGGL((step_wave_kernel<S, R, true, ODD, NT>), g, dim3(64), 0, s, a);
+  else hipLaunchKernelGGL((step_wave_kernel<S, R, false, ODD, NT>), g, dim3(64), 0, s, a);
 }
 
 template <int S, bool ODD, bool ST>
@@ -541,47 +584,61 @@ hipError_t launch_s(bool odd, int rounds, bool stats, const StepArgs& a, const L
   return stats ? launch_r<S, false, true>(rounds, a, l, s) : launch_r<S, false, false>(rounds, a, l, s);
 }
 
-template <int S, bool ST, bool ODD>
+template <int S, bool ST, bool ODD, bool NT>
 hipError_t launch_row_s(int rounds, const StepArgs& a, uint32_t grid, hipStream_t s) {
   const dim3 g(grid), blk(a.nx);
   switch (rounds) {
-    case 0: launch_row_g<S, 0, ST, ODD>(a, g, blk, s); break;
-    case 7: launch_row_g<S, 7, ST, ODD>(a, g, blk, s); break;
-    case 10: launch_row_g<S, 10, ST, ODD>(a, g, blk, s); break;
+    case 0: launch_row_g<S, 0, ST, ODD, NT>(a, g, blk, s); break;
+    case 7: launch_row_g<S, 7, ST, ODD, NT>(a, g, blk, s); break;
+    case 10: launch_row_g<S, 10, ST, ODD, NT>(a, g, blk, s); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
 // The even whole-row kernel runs only with statistics.
-template <int S>
+template <int S, bool NT>
 hipError_t launch_row_st(bool odd, bool stats, int rounds, const StepArgs& a, uint32_t grid, hipStream_t s) {
-  if (!odd) return stats ? launch_row_s<S, true, false>(rounds, a, grid, s) : hipErrorInvalidConfiguration;
-  return stats ? launch_row_s<S, true, true>(rounds, a, grid, s) : launch_row_s<S, false, true>(rounds, a, grid, s);
+  if (!odd) return stats ? launch_row_s<S, true, false, NT>(rounds, a, grid, s) : hipErrorInvalidConfiguration;
+  return stats ? launch_row_s<S, true, true, NT>(rounds, a, grid, s) : launch_row_s<S, false, true, NT>(rounds, a, grid, s);
 }
 
-template <int S>
+template <int S, bool ODD, bool NT>
 hipError_t launch_wave_s(int rounds, const StepArgs& a, uint32_t grid, hipStream_t s) {
   switch (rounds) {
-    case 0: launch_wave_g<S, 0>(a, dim3(grid), s); break;
-    case 7: launch_wave_g<S, 7>(a, dim3(grid), s); break;
-    case 10: launch_wave_g<S, 10>(a, dim3(grid), s); break;
+    case 0: launch_wave_g<S, 0, ODD, NT>(a, dim3(grid), s); break;
+    case 7: launch_wave_g<S, 7, ODD, NT>(a, dim3(grid), s); break;
+    case 10: launch_wave_g<S, 10, ODD, NT>(a, dim3(grid), s); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
+template <int S>
+hipError_t launch_wave_p(bool odd, int rounds, const StepArgs& a, uint32_t grid, hipStream_t s) {
+  if (odd) return launch_wave_s<S, true, false>(rounds, a, grid, s);  // odd steps keep the default policy
+  return streams(a) ? launch_wave_s<S, false, true>(rounds, a, grid, s) : launch_wave_s<S, false, false>(rounds, a, grid, s);
+}
+
+template <int S>
+hipError_t launch_row_p(bool odd, bool stats, int rounds, const StepArgs& a, uint32_t grid, hipStream_t s) {
+  return streams(a) ? launch_row_st<S, true>(odd, stats, rounds, a, grid, s)
+                    : launch_row_st<S, false>(odd, stats, rounds, a, grid, s);
+}
+
 }  // namespace
 
-hipError_t launch_step_wave(int storage, int rounds, const StepArgs& a, hipStream_t stream) {
+bool streams(const StepArgs& a) { return pop_span(a) > kStreamBytes; }
+
+hipError_t launch_step_wave(int storage, bool odd, int rounds, const StepArgs& a, hipStream_t stream) {
   if (a.nx % 64 != 0 || a.nx == 0) return hipErrorInvalidConfiguration;
   const uint64_t segs = static_cast<uint64_t>(a.nx / 64) * a.ny * a.nz;
   if (segs >= (1ull << 31)) return hipErrorInvalidConfiguration;
   const uint32_t grid = static_cast<uint32_t>((segs + 7) / 8 * 8);
   switch (storage) {
-    case kF32: return launch_wave_s<kF32>(rounds, a, grid, stream);
-    case kF16: return launch_wave_s<kF16>(rounds, a, grid, stream);
-    case kBF16: return launch_wave_s<kBF16>(rounds, a, grid, stream);
+    case kF32: return launch_wave_p<kF32>(odd, rounds, a, grid, stream);
+    case kF16: return launch_wave_p<kF16>(odd, rounds, a, grid, stream);
+    case kBF16: return launch_wave_p<kBF16>(odd, rounds, a, grid, stream);
     default: return hipErrorInvalidValue;
   }
 }
@@ -599,9 +656,29 @@ hipError_t launch_step_row(int storage, bool odd, int rounds, bool stats, const 
   if (rows >= (1ull << 31)) return hipErrorInvalidConfiguration;
   const uint32_t grid = row_grid(a.ny, a.nz);
   switch (storage) {
-    case kF32: return launch_row_st<kF32>(odd, stats, rounds, a, grid, stream);
-    case kF16: return launch_row_st<kF16>(odd, stats, rounds, a, grid, stream);
-    case kBF16: return launch_row_st<kBF16>(odd, stats, rounds, a, grid, stream);
+    case kF32: return launch_row_p<kF32>(odd, stats, rounds, a, grid, stream);
+    case kF16: return launch_row_p<kF16>(odd, stats, rounds, a, grid, stream);
+    case kBF16: return launch_row_p<kBF16>(odd, stats, rounds, a, grid, stream);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+bool flat_kernel_fits(const StepArgs& a) {
+  return a.nx % 64 != 0 && pop_span(a) < (1ull << 32);
+}
+
+uint32_t flat_grid(const StepArgs& a, bool stats) {
+  const uint32_t blk = stats ? kBlock : 64;
+  return ((a.nx * a.ny * a.nz + blk - 1) / blk + 7) / 8 * 8;
+}
+
+hipError_t launch_step_flat(int storage, bool odd, int rounds, bool stats, const StepArgs& a, hipStream_t stream) {
+  if (!flat_kernel_fits(a)) return hipErrorInvalidConfiguration;
+  const uint32_t grid = flat_grid(a, stats);
+  switch (storage) {
+    case kF32: return launch_flat_s<kF32>(odd, rounds, stats, a, grid, stream);
+    case kF16: return launch_flat_s<kF16>(odd, rounds, stats, a, grid, stream);
+    case kBF16: return launch_flat_s<kBF16>(odd, rounds, stats, a, grid, stream);
     default: return hipErrorInvalidValue;
   }
 }
