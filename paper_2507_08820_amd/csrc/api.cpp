@@ -10,16 +10,16 @@
 #include <cstring>
 #include <new>
 #include <string>
+#include <vector>
 
 #include "../../include/rflbm.h"
 #include "d3q27.hpp"
 #include "kernels.hpp"
 #include "lattice.hpp"
+#include "sk.hpp"
 #include "storage.hpp"
 
 namespace rflbm {
-hipError_t launch_sk_bin(const void* spec, uint32_t nx, uint32_t ny, uint32_t nz, uint32_t nshells,
-                         double* shell_sum, unsigned long long* shell_count, hipStream_t s);
 // Moves the stored state to the other AA parity in place, as raw stored words.
 hipError_t launch_swap_parity(int storage, const GatherArgs& g, hipStream_t s);
 }
@@ -286,12 +286,19 @@ void lattice_release(rflbm_lattice* L) {
   if (L->sk_spec) (void)hipFree(L->sk_spec);
   if (L->sk_sums) (void)hipFree(L->sk_sums);
   if (L->sk_counts) (void)hipFree(L->sk_counts);
+  if (L->sk_twiddle) (void)hipFree(L->sk_twiddle);
+  if (L->sk_partial) (void)hipFree(L->sk_partial);
+  if (L->sk_host) (void)hipHostFree(L->sk_host);
   if (L->owns_buf) (void)hipFree(L->buf);
   L->have_plan = false;
   L->sk_fields = nullptr;
   L->sk_spec = nullptr;
   L->sk_sums = nullptr;
   L->sk_counts = nullptr;
+  L->sk_twiddle = nullptr;
+  L->sk_partial = nullptr;
+  L->sk_host = nullptr;
+  L->sk_ready = false;
   L->buf = nullptr;
 }
 
@@ -637,29 +644,55 @@ int32_t rflbm_sk_nshells(const rflbm_lattice* L) {
   return static_cast<int32_t>(std::llround(h)) + 1;
 }
 
+// exp(-2 pi i t / n), t < n, for the three sides one after another.
+static std::vector<float2> sk_twiddles(const rflbm_params& p) {
+  std::vector<float2> w;
+  for (int32_t n : {p.nx, p.ny, p.nz})
+    for (int32_t t = 0; t < n; ++t) {
+      const double a = -2.0 * M_PI * t / n;
+      w.push_back(make_float2(static_cast<float>(std::cos(a)), static_cast<float>(std::sin(a))));
+    }
+  return w;
+}
+
 static rflbm_status sk_prepare(rflbm_lattice* L) {
-  if (L->have_plan) return RFLBM_OK;
+  if (L->sk_ready) return RFLBM_OK;
   const uint64_t N = nodes(L);
   L->nshells = rflbm_sk_nshells(L);
-  const size_t spec_bytes = static_cast<size_t>(L->p.nx / 2 + 1) * L->p.ny * L->p.nz * 2 * sizeof(float);
-  // buffers that an earlier, failed attempt allocated are kept and reused
-  if (!L->sk_fields) RFLBM_HIP(hipMalloc(reinterpret_cast<void**>(&L->sk_fields), 10 * N * sizeof(float)));
-  if (!L->sk_spec) RFLBM_HIP(hipMalloc(&L->sk_spec, spec_bytes));
-  if (!L->sk_sums) RFLBM_HIP(hipMalloc(reinterpret_cast<void**>(&L->sk_sums), 10 * L->nshells * sizeof(double)));
-  if (!L->sk_counts)
-    RFLBM_HIP(hipMalloc(reinterpret_cast<void**>(&L->sk_counts), L->nshells * sizeof(unsigned long long)));
-  RFLBM_HIP(hipMemsetAsync(L->sk_sums, 0, 10 * L->nshells * sizeof(double), L->stream));
-  RFLBM_HIP(hipMemsetAsync(L->sk_counts, 0, L->nshells * sizeof(unsigned long long), L->stream));
-  hipfftHandle plan;
-  if (hipfftPlan3d(&plan, L->p.nz, L->p.ny, L->p.nx, HIPFFT_R2C) != HIPFFT_SUCCESS)
-    return fail(RFLBM_EHIP, "hipfftPlan3d failed");
-  // the plan is kept only once it runs on the lattice stream
-  if (hipfftSetStream(plan, L->stream) != HIPFFT_SUCCESS) {
-    (void)hipfftDestroy(plan);
-    return fail(RFLBM_EHIP, "hipfftSetStream failed");
+  L->sk_own = sk_fits(L->p.nx, L->p.ny, L->p.nz);
+  const size_t spec_bytes = sizeof(float2) * (L->sk_own ? 10 : 1) * (L->p.nx / 2 + 1) * L->p.ny * L->p.nz;
+  const auto take = [](auto** ptr, size_t bytes) {
+    // buffers that an earlier, failed attempt allocated are kept and reused
+    return *ptr ? hipSuccess : hipMalloc(reinterpret_cast<void**>(ptr), bytes);
+  };
+  RFLBM_HIP(take(&L->sk_spec, spec_bytes));
+  RFLBM_HIP(take(&L->sk_sums, 10 * L->nshells * sizeof(double)));
+  RFLBM_HIP(take(&L->sk_counts, L->nshells * sizeof(unsigned long long)));
+  if (!L->sk_host)
+    RFLBM_HIP(hipHostMalloc(reinterpret_cast<void**>(&L->sk_host), 2 * L->nshells * sizeof(double), hipHostMallocDefault));
+  RFLBM_HIP(launch_fill_zero(L->sk_sums, 10 * static_cast<size_t>(L->nshells), L->stream));
+  RFLBM_HIP(launch_fill_zero(reinterpret_cast<double*>(L->sk_counts), L->nshells, L->stream));
+  RFLBM_HIP(launch_sk_count(L->p.nx, L->p.ny, L->p.nz, L->nshells, L->sk_counts, L->stream));
+  if (L->sk_own) {
+    const std::vector<float2> w = sk_twiddles(L->p);
+    RFLBM_HIP(take(&L->sk_twiddle, w.size() * sizeof(float2)));
+    RFLBM_HIP(take(&L->sk_partial, 10 * sizeof(double) * L->nshells * sk_blocks(L->p.nx, L->p.ny, L->p.nz)));
+    RFLBM_HIP(hipMemcpyAsync(L->sk_twiddle, w.data(), w.size() * sizeof(float2), hipMemcpyHostToDevice, L->stream));
+    RFLBM_HIP(hipStreamSynchronize(L->stream));
+  } else {
+    RFLBM_HIP(take(&L->sk_fields, 10 * N * sizeof(float)));
+    hipfftHandle plan;
+    if (hipfftPlan3d(&plan, L->p.nz, L->p.ny, L->p.nx, HIPFFT_R2C) != HIPFFT_SUCCESS)
+      return fail(RFLBM_EHIP, "hipfftPlan3d failed");
+    // the plan is kept only once it runs on the lattice stream
+    if (hipfftSetStream(plan, L->stream) != HIPFFT_SUCCESS) {
+      (void)hipfftDestroy(plan);
+      return fail(RFLBM_EHIP, "hipfftSetStream failed");
+    }
+    L->plan = plan;
+    L->have_plan = true;
   }
-  L->plan = plan;
-  L->have_plan = true;
+  L->sk_ready = true;
   L->sk_samples = 0;
   return RFLBM_OK;
 }
@@ -667,13 +700,21 @@ static rflbm_status sk_prepare(rflbm_lattice* L) {
 rflbm_status rflbm_sk_sample(rflbm_lattice* L) {
   if (rflbm_status s = check_lattice(L)) return s;
   if (rflbm_status s = sk_prepare(L)) return s;
-  const uint64_t N = nodes(L);
-  RFLBM_HIP(launch_get_moments(L->p.storage, gather_args(L, L->p, L->t), 7u, L->sk_fields, L->stream));
-  for (int f = 0; f < 10; ++f) {
-    if (hipfftExecR2C(L->plan, L->sk_fields + f * N, static_cast<hipfftComplex*>(L->sk_spec)) != HIPFFT_SUCCESS)
-      return fail(RFLBM_EHIP, "hipfftExecR2C failed");
-    RFLBM_HIP(launch_sk_bin(L->sk_spec, L->p.nx, L->p.ny, L->p.nz, L->nshells, L->sk_sums + f * L->nshells,
-                            (L->sk_samples == 0 && f == 0) ? L->sk_counts : nullptr, L->stream));
+  const GatherArgs g = gather_args(L, L->p, L->t);
+  if (L->sk_own) {
+    RFLBM_HIP(launch_sk(L->p.storage, g, L->sk_twiddle, L->nshells, static_cast<float2*>(L->sk_spec), L->sk_partial,
+                        L->sk_sums, L->stream));
+  } else {
+    const uint64_t N = nodes(L);
+    GatherArgs dev = g;
+    dev.rho0 = 0.0;  // rho - rho0, whose FP32 digits the mean would take
+    RFLBM_HIP(launch_get_moments(L->p.storage, dev, 7u, L->sk_fields, L->stream));
+    for (int f = 0; f < 10; ++f) {
+      if (hipfftExecR2C(L->plan, L->sk_fields + f * N, static_cast<hipfftComplex*>(L->sk_spec)) != HIPFFT_SUCCESS)
+        return fail(RFLBM_EHIP, "hipfftExecR2C failed");
+      RFLBM_HIP(launch_sk_bin(L->sk_spec, L->p.nx, L->p.ny, L->p.nz, L->nshells, L->sk_sums + f * L->nshells,
+                              L->stream));
+    }
   }
   L->sk_samples += 1;
   return RFLBM_OK;
@@ -685,26 +726,22 @@ rflbm_status rflbm_get_sk(rflbm_lattice* L, int32_t field, double* shell_sum, in
   if (field < 0 || field >= 10) return fail(RFLBM_EINVAL, "field must be 0..9");
   if (nshells != rflbm_sk_nshells(L)) return fail(RFLBM_EINVAL, "nshells must equal rflbm_sk_nshells");
   if (samples) *samples = L->sk_samples;
-  if (!L->have_plan || L->sk_samples == 0) {
+  if (!L->sk_ready || L->sk_samples == 0) {
     if (shell_sum) std::memset(shell_sum, 0, nshells * sizeof(double));
     if (shell_count) std::memset(shell_count, 0, nshells * sizeof(int64_t));
     return RFLBM_OK;
   }
-  if (shell_sum)
-    RFLBM_HIP(hipMemcpyAsync(shell_sum, L->sk_sums + field * L->nshells, nshells * sizeof(double),
-                             hipMemcpyDeviceToHost, L->stream));
-  if (shell_count)
-    RFLBM_HIP(hipMemcpyAsync(shell_count, L->sk_counts, nshells * sizeof(int64_t), hipMemcpyDeviceToHost,
-                             L->stream));
+  RFLBM_HIP(launch_sk_read(L->sk_sums + field * L->nshells, L->sk_counts, L->nshells, L->sk_host, L->stream));
   RFLBM_HIP(hipStreamSynchronize(L->stream));
+  if (shell_sum) std::memcpy(shell_sum, L->sk_host, nshells * sizeof(double));
+  if (shell_count) std::memcpy(shell_count, L->sk_host + nshells, nshells * sizeof(int64_t));
   return RFLBM_OK;
 }
 
 rflbm_status rflbm_reset_sk(rflbm_lattice* L) {
   if (rflbm_status s = check_lattice(L)) return s;
-  if (!L->have_plan) return RFLBM_OK;
-  RFLBM_HIP(hipMemsetAsync(L->sk_sums, 0, 10 * L->nshells * sizeof(double), L->stream));
-  RFLBM_HIP(hipMemsetAsync(L->sk_counts, 0, L->nshells * sizeof(unsigned long long), L->stream));
+  if (!L->sk_ready) return RFLBM_OK;
+  RFLBM_HIP(launch_fill_zero(L->sk_sums, 10 * static_cast<size_t>(L->nshells), L->stream));
   L->sk_samples = 0;
   return RFLBM_OK;
 }

@@ -72,12 +72,17 @@ struct rflbm_lattice {
   // in one-wave x-segments, odd steps in whole-row blocks when nx fits
   bool row_mode = true;
   // S(k) state (library-allocated on first use)
+  bool sk_ready = false;
+  bool sk_own = false;                      // sides that the transforms in LDS take; else hipFFT
   hipfftHandle plan = 0;
   bool have_plan = false;
-  float* sk_fields = nullptr;               // 10 N floats
-  void* sk_spec = nullptr;                  // nz ny (nx/2 + 1) complex
+  float* sk_fields = nullptr;               // hipFFT: 10 N floats
+  void* sk_spec = nullptr;                  // nz ny (nx/2 + 1) complex, for every field or (hipFFT) one
+  float2* sk_twiddle = nullptr;             // nx + ny + nz
+  double* sk_partial = nullptr;             // 10 sk_blocks nshells
   double* sk_sums = nullptr;                // 10 nshells
-  unsigned long long* sk_counts = nullptr;  // nshells
+  unsigned long long* sk_counts = nullptr;  // nshells, set once (they depend on the box alone)
+  double* sk_host = nullptr;                // 2 nshells, pinned: readback of one field
   int64_t sk_samples = 0;
   int32_t nshells = 0;
 };
