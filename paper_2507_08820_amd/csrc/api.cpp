@@ -97,6 +97,9 @@ uint64_t plane_pitch_of(const rflbm_params& p) {
 // step, a sequential walk in either layout, is unchanged (4.73 ms).
 constexpr uint32_t kBrickYLog = 1, kBrickZLog = 4;
 
+// Most device memory that the partials of several sampled steps may take.
+constexpr size_t kStatBytes = 4ull << 20;
+
 static void brick_shape(const rflbm_params& p, uint32_t& by_log, uint32_t& bz_log) {
   by_log = kBrickYLog;
   while (by_log > 0 && p.ny % (1 << by_log) != 0) --by_log;
@@ -125,7 +128,11 @@ Layout layout_for(const rflbm_params& p, bool bricks) {
   L.flag_off = L.pop_bytes;
   L.acc_off = L.flag_off + kAlign;
   L.partial_off = L.acc_off + align_up(kAccDoubles * sizeof(double), kAlign);
-  L.scratch_off = L.partial_off + align_up(static_cast<size_t>(kNumStats) * L.grid_max * sizeof(double), kAlign);
+  // single boxes: partials of up to 32 sampled steps, to be added in one launch
+  const size_t slot = static_cast<size_t>(kNumStats) * L.grid_max * sizeof(double);
+  L.stat_slots = 1;
+  while (bricks && L.stat_slots < 32 && (L.stat_slots + 1) * slot <= kStatBytes) ++L.stat_slots;
+  L.scratch_off = L.partial_off + align_up(L.stat_slots * slot, kAlign);
   const size_t chunks = (L.grid_max + 2047) / 2048;
   L.total = L.scratch_off + align_up(2 * static_cast<size_t>(kNumStats) * chunks * sizeof(double), kAlign);
   return L;
@@ -361,28 +368,49 @@ rflbm_status lattice_steps(rflbm_lattice* L, int64_t nsteps) {
   const int rounds = L->p.kT > 0.0 ? static_cast<int>(L->p.philox_rounds) : 0;
   double* acc = reinterpret_cast<double*>(L->buf + L->L.acc_off);
   double* scratch = reinterpret_cast<double*>(L->buf + L->L.scratch_off);
+  // statistics partials waiting in the slots: all of one grid size
+  double* const partials = a.partials;
+  const uint64_t slot_pitch = static_cast<uint64_t>(kNumStats) * L->L.grid_max;
+  uint32_t waiting = 0, waiting_grid = 0;
+  const auto fold = [&]() {
+    const hipError_t e = launch_stats_fold(partials, waiting_grid, slot_pitch, waiting, scratch, acc, L->stream);
+    waiting = 0;
+    return e;
+  };
   for (int64_t s = 0; s < nsteps; ++s) {
     const int64_t t = L->t;
     const bool stats = L->stats_every > 0 && (t % L->stats_every) == 0;
     a.step = static_cast<uint32_t>(t & 0xffffffffu);
     const bool odd = (t & 1) != 0;
+    a.partials = partials + waiting * slot_pitch;
     uint32_t grid = L->launch.grid;  // blocks, hence statistics partials, of the kernel used
+    hipError_t e;
     if (L->row_mode && flat_kernel_fits(a)) {
-      RFLBM_HIP(launch_step_flat(L->p.storage, odd, rounds, stats, a, L->stream));
+      e = launch_step_flat(L->p.storage, odd, rounds, stats, a, L->stream);
       grid = flat_grid(a, stats);
     } else if ((odd || stats) && odd_in_rows(L)) {
       // whole rows: odd steps, and even steps with statistics (one partial per
       // row; the one-wave even blocks would write one per wave)
-      RFLBM_HIP(launch_step_row(L->p.storage, odd, rounds, stats, a, L->stream));
+      e = launch_step_row(L->p.storage, odd, rounds, stats, a, L->stream);
       grid = row_grid(L->p.ny, L->p.nz);
     } else if (!stats && in_waves(L, a, odd)) {
-      RFLBM_HIP(launch_step_wave(L->p.storage, odd, rounds, a, L->stream));
+      e = launch_step_wave(L->p.storage, odd, rounds, a, L->stream);
     } else {
-      RFLBM_HIP(launch_step(L->p.storage, odd, rounds, stats, a, L->launch, L->stream));
+      e = launch_step(L->p.storage, odd, rounds, stats, a, L->launch, L->stream);
     }
-    if (stats) RFLBM_HIP(launch_stats_reduce(a.partials, grid, scratch, acc, L->stream));
+    if (e != hipSuccess) {
+      (void)fold();  // the steps before it count
+      return hip_fail(RFLBM_EHIP, "step", e);
+    }
+    if (stats) {
+      // even and odd steps of a lattice have the same number of blocks
+      waiting_grid = grid;
+      ++waiting;
+      if (grid > fold_limit() || waiting == L->L.stat_slots) RFLBM_HIP(fold());
+    }
     L->t = t + 1;
   }
+  RFLBM_HIP(fold());
   return RFLBM_OK;
 }
 

@@ -161,10 +161,13 @@ bool flat_kernel_fits(const StepArgs& a);
 hipError_t launch_step_flat(int storage, bool odd, int rounds, bool stats, const StepArgs& a, hipStream_t stream);
 uint32_t flat_grid(const StepArgs& a, bool stats);
 
-// Deterministic reduction of the statistics partials into the accumulators.
-// scratch holds at least 2 * kNumStats * ceil(grid / 2048) doubles.
-hipError_t launch_stats_reduce(const double* partials, uint32_t grid, double* scratch,
-                               double* acc, hipStream_t stream);
+// Adds the statistics partials of `slots` sampled steps (slot_pitch doubles
+// apart, [kNumStats][grid] each) to the accumulators, in a fixed order.  More
+// than one slot needs grid <= fold_limit().  scratch holds at least
+// 2 * kNumStats * ceil(grid / 2048) doubles.
+hipError_t launch_stats_fold(const double* partials, uint32_t grid, uint64_t slot_pitch, uint32_t slots,
+                             double* scratch, double* acc, hipStream_t stream);
+uint32_t fold_limit();
 
 struct GatherArgs {
   const void* pop;

@@ -24,6 +24,7 @@ struct Layout {
   size_t pop_bytes;
   size_t flag_off, acc_off, partial_off, scratch_off, total;
   uint32_t grid_max;
+  uint32_t stat_slots;   // sampled steps whose partials fit (kNumStats grid_max doubles each)
 };
 
 constexpr size_t kAlign = 256;

@@ -46,6 +46,13 @@ namespace {
 
 constexpr int kBlock = 256;
 
+// Staged statistics, one LDS row per column: node `tid` at stat_at(tid).  The gap
+// after every 32 puts the values that the summing threads (8 parts of 32 nodes
+// for each column) read together on different banks; without it 32 of them
+// meet on one.
+constexpr int kStatPitch = kBlock + kBlock / 32;
+__device__ __forceinline__ constexpr uint32_t stat_at(uint32_t tid) { return tid + (tid >> 5); }
+
 
 // Cache policy of the population accesses (NT in the kernels' scope: non-temporal).
 // Even steps, and odd steps in whole rows, read and write whole cache lines
@@ -200,14 +207,14 @@ __device__ __forceinline__ void row_shift(uint32_t (&v)[kQ], uint32_t (*edge)[kM
 
 // Block sums of the staged statistics in FP64, fixed order (8 partial sums of 32
 // nodes per column), into column entry blockIdx.x of the partials.
-__device__ __forceinline__ void block_stats(const float (*stat_lds)[kBlock], uint32_t tid, double* partials) {
+__device__ __forceinline__ void block_stats(const float (*stat_lds)[kStatPitch], uint32_t tid, double* partials) {
   __shared__ double part[kNumStats][8];
   __syncthreads();
   if (tid < kNumStats * 8) {
     const int c = tid >> 3, p = tid & 7;
     double acc = 0.0;
 #pragma unroll 8
-    for (int e = 0; e < 32; ++e) acc += static_cast<double>(stat_lds[c][p * 32 + e]);
+    for (int e = 0; e < 32; ++e) acc += static_cast<double>(stat_lds[c][stat_at(p * 32) + e]);
     part[c][p] = acc;
   }
   __syncthreads();
@@ -239,7 +246,7 @@ __global__ void __launch_bounds__(kBlock) step_kernel(const StepArgs a) {
   const uint32_t tid = threadIdx.x + blockDim.x * threadIdx.y;
   const bool active = tile < a.ntiles && x < a.nx && y < a.ny;
 
-  __shared__ float stat_lds[STATS ? kNumStats : 1][kBlock];
+  __shared__ float stat_lds[STATS ? kNumStats : 1][kStatPitch];
 
   if (active) {
     const uint32_t step = a.step;
@@ -255,7 +262,7 @@ __global__ void __launch_bounds__(kBlock) step_kernel(const StepArgs a) {
 #include "node_body.inc"
   } else if constexpr (STATS) {
 #pragma unroll
-    for (int c = 0; c < kNumStats; ++c) stat_lds[c][tid] = 0.0f;
+    for (int c = 0; c < kNumStats; ++c) stat_lds[c][stat_at(tid)] = 0.0f;
   }
 
   if constexpr (STATS) block_stats(stat_lds, tid, a.partials);
@@ -277,7 +284,7 @@ __global__ void __launch_bounds__(STATS ? kBlock : 64) step_flat_kernel(const St
   if (a.xcd_remap) tile = (tile & 7u) * (gridDim.x >> 3) + (tile >> 3);
   const uint32_t tid = threadIdx.x;
   const uint32_t m = tile * BLOCK + tid;
-  __shared__ float stat_lds[STATS ? kNumStats : 1][kBlock];
+  __shared__ float stat_lds[STATS ? kNumStats : 1][kStatPitch];
   if (m < a.nx * a.ny * a.nz) {
     const uint32_t row = fast_div(m, a.div_nx);
     const uint32_t x = m - row * a.nx;
@@ -297,7 +304,7 @@ __global__ void __launch_bounds__(STATS ? kBlock : 64) step_flat_kernel(const St
 #include "node_body.inc"
   } else if constexpr (STATS) {
 #pragma unroll
-    for (int c = 0; c < kNumStats; ++c) stat_lds[c][tid] = 0.0f;
+    for (int c = 0; c < kNumStats; ++c) stat_lds[c][stat_at(tid)] = 0.0f;
   }
   if constexpr (STATS) block_stats(stat_lds, tid, a.partials);
 }
@@ -310,7 +317,7 @@ __global__ void __launch_bounds__(64) step_wave_kernel(const StepArgs a) {
   constexpr bool STATS = false, SMALL_BOX = false, ROW_SHIFT = false, BUFFER_ACCESS = true;
   constexpr bool BRICKS = true;
   constexpr bool GHOST_EQ = GEQ, STATS_WAVE = false;
-  [[maybe_unused]] float (*stat_lds)[kBlock] = nullptr;
+  [[maybe_unused]] float (*stat_lds)[kStatPitch] = nullptr;
   [[maybe_unused]] float (*stat_wave)[kMaxRowWaves] = nullptr;
   [[maybe_unused]] const uint32_t tid = 0;
   [[maybe_unused]] uint32_t (*row_edge_in)[kMaxRowWaves] = nullptr;
@@ -339,7 +346,7 @@ template <int S, int ROUNDS, bool GEQ, bool STATS, bool ODD, bool NT>
 __global__ void __launch_bounds__(kMaxRowWaves * 64) step_row_kernel(const StepArgs a) {
   constexpr bool SMALL_BOX = false, ROW_SHIFT = ODD, BUFFER_ACCESS = true, BRICKS = true;
   constexpr bool GHOST_EQ = GEQ, STATS_WAVE = true;
-  [[maybe_unused]] float (*stat_lds)[kBlock] = nullptr;
+  [[maybe_unused]] float (*stat_lds)[kStatPitch] = nullptr;
   [[maybe_unused]] const uint32_t tid = 0;
   __shared__ uint32_t row_edge_in[18][kMaxRowWaves];   // gather (stored words)
   __shared__ uint32_t row_edge_out[18][kMaxRowWaves];  // scatter (FP32 values)
@@ -409,7 +416,7 @@ __global__ void __launch_bounds__(kBlock) batch_kernel(const BatchArgs b) {
   constexpr bool ROW_SHIFT = false, NT = true;
   [[maybe_unused]] uint32_t (*row_edge_in)[kMaxRowWaves] = nullptr;
   [[maybe_unused]] uint32_t (*row_edge_out)[kMaxRowWaves] = nullptr;
-  __shared__ float stat_lds[STATS ? kNumStats : 1][kBlock];
+  __shared__ float stat_lds[STATS ? kNumStats : 1][kStatPitch];
   __shared__ double stat_part[STATS ? kNumStats : 1][kBlock / 32];
   const uint32_t tid = threadIdx.x;
   // the tables are read-only for the whole launch: constant address space,
@@ -432,7 +439,7 @@ __global__ void __launch_bounds__(kBlock) batch_kernel(const BatchArgs b) {
 #include "node_body.inc"
     } else if constexpr (STATS) {
 #pragma unroll
-      for (int c = 0; c < kNumStats; ++c) stat_lds[c][tid] = 0.0f;
+      for (int c = 0; c < kNumStats; ++c) stat_lds[c][stat_at(tid)] = 0.0f;
     }
     if constexpr (STATS) {
       // parts of 32 nodes per column, then the parts in order, in FP64
@@ -442,7 +449,7 @@ __global__ void __launch_bounds__(kBlock) batch_kernel(const BatchArgs b) {
         const uint32_t c = tid / parts, p = tid - c * parts;
         double acc = 0.0;
 #pragma unroll 8
-        for (int e = 0; e < 32; ++e) acc += static_cast<double>(stat_lds[c][p * 32 + e]);
+        for (int e = 0; e < 32; ++e) acc += static_cast<double>(stat_lds[c][stat_at(p * 32) + e]);
         stat_part[c][p] = acc;
       }
       __syncthreads();
@@ -510,16 +517,55 @@ __global__ void __launch_bounds__(256) reduce_columns(const double* in, uint32_t
   if (threadIdx.x == 0) out[static_cast<size_t>(blockIdx.y) * n_out + blockIdx.x] = sh[0];
 }
 
-// acc[0..22] += sums; acc[23] += 1 (samples); acc[24] = mass; acc[25..27] = momentum.
-__global__ void accumulate_stats(const double* sums, double* acc) {
-  const int c = threadIdx.x;
-  if (c < kNumStats) acc[c] += sums[c];
-  if (c == 0) {
-    acc[kNumStats] += 1.0;
-    acc[kNumStats + 1] = sums[0];
-    acc[kNumStats + 2] = sums[2];
-    acc[kNumStats + 3] = sums[3];
-    acc[kNumStats + 4] = sums[4];
+// Adds the partials of `slots` sampled steps, in their order, to the accumulators:
+// block c sums column c of every slot ([kNumStats][n], n <= kFoldLimit, in the
+// order of reduce_columns) and adds the sums one by one.  acc[0..22] +=
+// sums; acc[23] += slots; acc[24] = mass, acc[25..27] = momentum of the last.
+// One launch for all sampled steps of a call: a launch takes 4 to 5 us, as long
+// as a step of a small box (statistics on every step, us per step: 16^3 10.3 ->
+// 6.3, 64^3 FP32 20.8 -> 13.4, 130 x 50 x 70 BF16 30.5 -> 16.1 with flat blocks).
+constexpr uint32_t kFoldTogether = 8;  // slots summed side by side
+constexpr uint32_t kFoldLimit = 8192;  // 32 values a thread and slot, about 4 us; more go through reduce_columns first
+
+__global__ void __launch_bounds__(256) fold_stats(const double* partials, uint32_t n, uint64_t slot_pitch,
+                                                  uint32_t slots, double* acc) {
+  __shared__ double sh[kFoldTogether][256];
+  const uint32_t c = blockIdx.x, tid = threadIdx.x;
+  double total = tid == 0 ? acc[c] : 0.0, last = 0.0;
+  for (uint32_t s0 = 0; s0 < slots; s0 += kFoldTogether) {
+#pragma unroll
+    for (uint32_t q = 0; q < kFoldTogether; ++q) {
+      double v = 0.0;
+      if (s0 + q < slots) {
+        const double* col = partials + (s0 + q) * slot_pitch + static_cast<size_t>(c) * n;
+#pragma unroll 8
+        for (uint32_t i = tid; i < n; i += 256) v += col[i];
+      }
+      sh[q][tid] = v;
+    }
+    __syncthreads();
+    for (uint32_t s = 128; s > 0; s >>= 1) {
+      if (tid < s) {
+#pragma unroll
+        for (uint32_t q = 0; q < kFoldTogether; ++q) sh[q][tid] += sh[q][tid + s];
+      }
+      __syncthreads();
+    }
+    if (tid == 0) {
+      for (uint32_t q = 0; q < kFoldTogether && s0 + q < slots; ++q) {
+        last = sh[q][0];
+        total += last;
+      }
+    }
+    __syncthreads();
+  }
+  if (tid == 0) {
+    acc[c] = total;
+    if (c == 0) {
+      acc[kNumStats] += static_cast<double>(slots);
+      acc[kNumStats + 1] = last;
+    }
+    if (c >= 2 && c <= 4) acc[kNumStats + c] = last;
   }
 }
 
@@ -756,14 +802,18 @@ hipError_t launch_advance_step(uint32_t* step, uint32_t delta, hipStream_t strea
   return hipGetLastError();
 }
 
-hipError_t launch_stats_reduce(const double* partials, uint32_t grid, double* scratch, double* acc,
-                               hipStream_t stream) {
+uint32_t fold_limit() { return kFoldLimit; }
+
+hipError_t launch_stats_fold(const double* partials, uint32_t grid, uint64_t slot_pitch, uint32_t slots,
+                             double* scratch, double* acc, hipStream_t stream) {
+  if (slots == 0) return hipSuccess;
+  if (grid > kFoldLimit && slots != 1) return hipErrorInvalidValue;
   const double* in = partials;
   uint32_t n = grid;
   double* bufs[2] = {scratch, scratch + static_cast<size_t>(kNumStats) *
                                             ((grid + kReduceChunk - 1) / kReduceChunk)};
   int which = 0;
-  while (n > 1) {
+  while (n > kFoldLimit) {
     const uint32_t n_out = (n + kReduceChunk - 1) / kReduceChunk;
     hipLaunchKernelGGL(reduce_columns, dim3(n_out, kNumStats), dim3(256), 0, stream, in, n,
                        bufs[which], n_out);
@@ -771,7 +821,7 @@ hipError_t launch_stats_reduce(const double* partials, uint32_t grid, double* sc
     which ^= 1;
     n = n_out;
   }
-  hipLaunchKernelGGL(accumulate_stats, dim3(1), dim3(64), 0, stream, in, acc);
+  hipLaunchKernelGGL(fold_stats, dim3(kNumStats), dim3(256), 0, stream, in, n, slot_pitch, slots, acc);
   return hipGetLastError();
 }
 

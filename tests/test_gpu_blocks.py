@@ -63,3 +63,24 @@ def test_boxes_beyond_the_cache(rf, storage, dims):
     a, _ = run(rf, dims, True, 3, **kw)
     b, _ = run(rf, dims, False, 3, **kw)
     assert bool((a == b).all())
+
+
+@pytest.mark.parametrize("storage,dims", [("f32", (16, 16, 16)), ("f32", (2, 3, 2)), ("f16", (64, 9, 16)),
+                                          ("f32", (64, 64, 40)), ("f32", (17, 19, 23))])
+def test_statistics_of_one_call_and_of_many(rf, storage, dims):
+    """The partials of a call's sampled steps are added together at its end, in
+    more than one batch where they exceed their slots: the sums are bit for bit
+    those of one call per step."""
+    lats = [rf.Lattice(dims, storage=storage, kT=1e-4, tau=0.7, seed=2) for _ in range(2)]
+    for lat in lats:
+        lat.init_thermal()
+        lat.stats_config(1)
+    lats[0].step(70)
+    for _ in range(70):
+        lats[1].step(1)
+    a, b = (lat.stats() for lat in lats)
+    assert a["samples"] == 70
+    for k in a:
+        np.testing.assert_array_equal(a[k], b[k], err_msg=k)
+    for lat in lats:
+        lat.close()
