@@ -91,23 +91,28 @@ __device__ __forceinline__ float angle_uniform(const Word4& w) { return angle_on
 
 constexpr float kMinus2Ln2 = -1.38629436111989061883f;  // -2 ln 2
 
-// Box-Muller pair m of a call, both normals multiplied by sqrt(c / (-2 ln 2)):
-// the radius is sqrt(c log2 U0), so c = -2 ln 2 gives standard normals and
-// c = -2 ln 2 rho gives sqrt(rho) times them.
+// Box-Muller pair m of a call: log2 U0 and the cosine and sine of 2 pi U1.
 template <int M>
-__device__ __forceinline__ void box_muller_scaled(const Word4& w, float c, float& z0, float& z1) {
+__device__ __forceinline__ void box_muller_parts(const Word4& w, float& log_u, float& cos_a, float& sin_a) {
   const uint32_t wr = M == 0 ? w.w0 : (M == 1 ? w.w1 : w.w2);
-  const float ur = radius_uniform(wr);
+  log_u = __builtin_amdgcn_logf(radius_uniform(wr));
   const float turns = angle_one_two<M>(w);  // 1 + the angle uniform, in revolutions
-  const float rad = __builtin_amdgcn_sqrtf(c * __builtin_amdgcn_logf(ur));
-  z0 = rad * __builtin_amdgcn_cosf(turns);
-  z1 = rad * __builtin_amdgcn_sinf(turns);
+  cos_a = __builtin_amdgcn_cosf(turns);
+  sin_a = __builtin_amdgcn_sinf(turns);
 }
+
+// The radius sqrt(c log2 U0): c = -2 ln 2 gives standard normals R cos, R sin, and
+// c = -2 ln 2 rho gives sqrt(rho) times them.
+__device__ __forceinline__ float box_muller_radius(float c, float log_u) { return __builtin_amdgcn_sqrtf(c * log_u); }
 
 // Standard normal Box-Muller pair m of a call.
 template <int M>
 __device__ __forceinline__ void box_muller(const Word4& w, float& z0, float& z1) {
-  box_muller_scaled<M>(w, kMinus2Ln2, z0, z1);
+  float log_u, cos_a, sin_a;
+  box_muller_parts<M>(w, log_u, cos_a, sin_a);
+  const float rad = box_muller_radius(kMinus2Ln2, log_u);
+  z0 = rad * cos_a;
+  z1 = rad * sin_a;
 }
 
 }  // namespace rflbm
