@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 #include <hipfft/hipfft.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -125,6 +126,9 @@ Layout layout_for(const rflbm_params& p, bool bricks) {
     const Launch l = make_launch(p.nx, p.ny, p.nz, bx, 256 / bx);
     if (l.grid > L.grid_max) L.grid_max = l.grid;
   }
+  // flat statistics steps of small boxes: a block per wave
+  if (node_count(p) <= kFlatWaveNodes)
+    L.grid_max = std::max(L.grid_max, static_cast<uint32_t>((node_count(p) + 63) / 64 + 7) / 8 * 8);
   L.flag_off = L.pop_bytes;
   L.acc_off = L.flag_off + kAlign;
   L.partial_off = L.acc_off + align_up(kAccDoubles * sizeof(double), kAlign);

@@ -82,6 +82,7 @@ struct rflbm_batch {
   int32_t n = 0;
   std::vector<rflbm_params> p;
   BatchLayout B;
+  uint64_t pop_bytes = 0;  // populations of all replicas
   uint8_t* buf = nullptr;
   bool owns_buf = false;
   hipStream_t stream = nullptr;
@@ -158,6 +159,7 @@ BatchArgs batch_args(const rflbm_batch* b, uint32_t step_offset) {
   a.step_offset = step_offset;
   a.partial_pitch = b->B.max_tiles;
   a.partials = reinterpret_cast<double*>(b->buf + b->B.partials_off);
+  a.pop_bytes = b->pop_bytes;
   return a;
 }
 
@@ -342,6 +344,7 @@ rflbm_status rflbm_batch_create(int32_t n, const rflbm_params* p, void* dev_buf,
     }
     lattice_init(v, p[r], b->buf + B.region_off[r], b->stream, false);  // plain layout
     v->is_view = true;
+    b->pop_bytes += v->L.pop_bytes;
     b->views.push_back(v);
     if (lattice_clear(v) != hipSuccess) {
       rflbm_batch_destroy(b);

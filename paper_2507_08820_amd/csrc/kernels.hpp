@@ -108,6 +108,7 @@ struct BatchArgs {
   uint32_t step_offset;                  // t mod 2^32 = *step + step_offset
   uint32_t partial_pitch;                // doubles between partial columns (>= ntiles)
   double* partials;                      // statistics partials [kNumStats][partial_pitch]
+  uint64_t pop_bytes;                    // populations of all replicas
 };
 
 // One step of every replica (persistent grid of `grid` blocks walking the tiles);
@@ -160,6 +161,8 @@ bool flat_kernel_fits(const StepArgs& a);
 // partial per block of the flat_grid(a, stats) blocks.
 hipError_t launch_step_flat(int storage, bool odd, int rounds, bool stats, const StepArgs& a, hipStream_t stream);
 uint32_t flat_grid(const StepArgs& a, bool stats);
+// Largest box whose flat statistics steps run in one-wave blocks.
+constexpr uint32_t kFlatWaveNodes = 1u << 14;
 
 // Adds the statistics partials of `slots` sampled steps (slot_pitch doubles
 // apart, [kNumStats][grid] each) to the accumulators, in a fixed order.  More

@@ -205,13 +205,15 @@ __device__ __forceinline__ void row_shift(uint32_t (&v)[kQ], uint32_t (*edge)[kM
   }
 }
 
-// Block sums of the staged statistics in FP64, fixed order (8 partial sums of 32
-// nodes per column), into column entry blockIdx.x of the partials.
+// Block sums of the staged statistics in FP64, fixed order (parts of 32 nodes per
+// column, then the parts in order), into column entry blockIdx.x of the partials.
+template <int BLOCK>
 __device__ __forceinline__ void block_stats(const float (*stat_lds)[kStatPitch], uint32_t tid, double* partials) {
-  __shared__ double part[kNumStats][8];
+  constexpr int kParts = BLOCK / 32;
+  __shared__ double part[kNumStats][kParts];
   __syncthreads();
-  if (tid < kNumStats * 8) {
-    const int c = tid >> 3, p = tid & 7;
+  if (tid < kNumStats * kParts) {
+    const int c = tid / kParts, p = tid % kParts;
     double acc = 0.0;
 #pragma unroll 8
     for (int e = 0; e < 32; ++e) acc += static_cast<double>(stat_lds[c][stat_at(p * 32) + e]);
@@ -221,7 +223,7 @@ __device__ __forceinline__ void block_stats(const float (*stat_lds)[kStatPitch],
   if (tid < kNumStats) {
     double acc = 0.0;
 #pragma unroll
-    for (int p = 0; p < 8; ++p) acc += part[tid][p];
+    for (int p = 0; p < kParts; ++p) acc += part[tid][p];
     partials[static_cast<size_t>(tid) * gridDim.x + blockIdx.x] = acc;
   }
 }
@@ -265,7 +267,7 @@ __global__ void __launch_bounds__(kBlock) step_kernel(const StepArgs a) {
     for (int c = 0; c < kNumStats; ++c) stat_lds[c][stat_at(tid)] = 0.0f;
   }
 
-  if constexpr (STATS) block_stats(stat_lds, tid, a.partials);
+  if constexpr (STATS) block_stats<kBlock>(stat_lds, tid, a.partials);
 }
 
 // One box whose rows do not fill whole waves, in blocks of consecutive nodes of
@@ -274,16 +276,17 @@ __global__ void __launch_bounds__(kBlock) step_kernel(const StepArgs a) {
 // step is, which left the lanes past each row's end idle (half of them at nx =
 // 130): us per step, tiled -> flat: 130 x 50 x 70 BF16 20.8 -> 12.8, FP32 26.7
 // -> 17.6; 96^3 FP32 36.4 -> 29.8, FP16 27.6 -> 21.0; 200^3 FP32 431 -> 341;
-// 300 x 280 x 260 BF16 795 -> 533.  Without statistics a block is one wave, so
-// that a small box spreads over more CUs: 17 x 19 x 23 FP32 4.4 us, in blocks of
-// 256 5.6, tiled 5.0; large boxes do not care.
-template <int S, bool ODD, int ROUNDS, bool STATS, bool GEQ>
-__global__ void __launch_bounds__(STATS ? kBlock : 64) step_flat_kernel(const StepArgs a) {
-  constexpr uint32_t BLOCK = STATS ? kBlock : 64;
+// 300 x 280 x 260 BF16 795 -> 533.  A block is one wave, so that a small box
+// spreads over more CUs: 17 x 19 x 23 FP32 4.4 us, in blocks of 256 5.6, tiled
+// 5.0; large boxes do not care, except with statistics, whose staging and
+// partials weigh more (us per step in blocks of 64 / 256: 16^3 5.3 / 6.1, 17 x 19
+// x 23 5.4 / 6.6, 48^3 FP16 11.8 / 8.1, 100^3 49 / 40; flat_block).
+template <int S, bool ODD, int ROUNDS, bool STATS, bool GEQ, int BLOCK>
+__global__ void __launch_bounds__(BLOCK) step_flat_kernel(const StepArgs a) {
   uint32_t tile = blockIdx.x;
   if (a.xcd_remap) tile = (tile & 7u) * (gridDim.x >> 3) + (tile >> 3);
   const uint32_t tid = threadIdx.x;
-  const uint32_t m = tile * BLOCK + tid;
+  const uint32_t m = tile * static_cast<uint32_t>(BLOCK) + tid;
   __shared__ float stat_lds[STATS ? kNumStats : 1][kStatPitch];
   if (m < a.nx * a.ny * a.nz) {
     const uint32_t row = fast_div(m, a.div_nx);
@@ -306,7 +309,7 @@ __global__ void __launch_bounds__(STATS ? kBlock : 64) step_flat_kernel(const St
 #pragma unroll
     for (int c = 0; c < kNumStats; ++c) stat_lds[c][stat_at(tid)] = 0.0f;
   }
-  if constexpr (STATS) block_stats(stat_lds, tid, a.partials);
+  if constexpr (STATS) block_stats<BLOCK>(stat_lds, tid, a.partials);
 }
 
 // Step without statistics in one-wave blocks: block b covers the 64
@@ -402,9 +405,13 @@ __global__ void __launch_bounds__(kMaxRowWaves * 64) step_row_kernel(const StepA
 // parity is a template parameter, and the host only replays graphs of an even
 // number of steps from an even step count.  GEQ: every replica has every
 // omega_g = 1; otherwise each replica's own setting is read at run time.
+// NT: even steps of FP32 batches beyond the memory-side cache (64 replicas of
+// 32^3..96^3, 2.3 GB: 826 us a step, 905 without); the rows of 16-bit replicas
+// are too short for whole lines (451 with, 438 without), and small batches stay
+// in the cache (24 of 8^3..32^3, FP32: 17.0 with, 13.4 without).
 // STATS: each tile's statistics are reduced in the block (fixed order, FP64)
 // into column t of b.partials, for batch_stats_reduce.
-template <int S, bool ODD, int ROUNDS, bool GEQ, bool STATS>
+template <int S, bool ODD, int ROUNDS, bool GEQ, bool STATS, bool NT>
 __global__ void __launch_bounds__(kBlock) batch_kernel(const BatchArgs b) {
   constexpr bool STATS_WAVE = false;
   [[maybe_unused]] float (*stat_wave)[kMaxRowWaves] = nullptr;
@@ -413,7 +420,7 @@ __global__ void __launch_bounds__(kBlock) batch_kernel(const BatchArgs b) {
   // buffer instructions measured faster for 16-bit storage, global ones for
   // FP32 (64 replicas of 32^3..96^3: 38.9 vs 36.6 and 24.6 vs 25.9 GLUPS)
   constexpr bool BUFFER_ACCESS = S != kF32;
-  constexpr bool ROW_SHIFT = false, NT = true;
+  constexpr bool ROW_SHIFT = false;
   [[maybe_unused]] uint32_t (*row_edge_in)[kMaxRowWaves] = nullptr;
   [[maybe_unused]] uint32_t (*row_edge_out)[kMaxRowWaves] = nullptr;
   __shared__ float stat_lds[STATS ? kNumStats : 1][kStatPitch];
@@ -578,10 +585,23 @@ hipError_t launch_t(const StepArgs& a, const Launch& l, hipStream_t s) {
   return hipGetLastError();
 }
 
+// Nodes per block of a flat step.
+uint32_t flat_block(const StepArgs& a, bool stats) {
+  return stats && a.nx * a.ny * a.nz > kFlatWaveNodes ? kBlock : 64;
+}
+
+template <int S, bool ODD, int R, bool ST, int BLOCK>
+void launch_flat_b(const StepArgs& a, uint32_t grid, hipStream_t s) {
+  if (a.ghost_eq) hipLaunchKernelGGL((step_flat_kernel<S, ODD, R, ST, true, BLOCK>), dim3(grid), dim3(BLOCK), 0, s, a);
+  else hipLaunchKernelGGL((step_flat_kernel<S, ODD, R, ST, false, BLOCK>), dim3(grid), dim3(BLOCK), 0, s, a);
+}
+
 template <int S, bool ODD, int R, bool ST>
 void launch_flat_t(const StepArgs& a, uint32_t grid, hipStream_t s) {
-  if (a.ghost_eq) hipLaunchKernelGGL((step_flat_kernel<S, ODD, R, ST, true>), dim3(grid), dim3(ST ? kBlock : 64), 0, s, a);
-  else hipLaunchKernelGGL((step_flat_kernel<S, ODD, R, ST, false>), dim3(grid), dim3(ST ? kBlock : 64), 0, s, a);
+  if constexpr (ST) {
+    if (flat_block(a, true) == kBlock) return launch_flat_b<S, ODD, R, ST, kBlock>(a, grid, s);
+  }
+  launch_flat_b<S, ODD, R, ST, 64>(a, grid, s);
 }
 
 template <int S, bool ODD, bool ST>
@@ -714,7 +734,7 @@ bool flat_kernel_fits(const StepArgs& a) {
 }
 
 uint32_t flat_grid(const StepArgs& a, bool stats) {
-  const uint32_t blk = stats ? kBlock : 64;
+  const uint32_t blk = flat_block(a, stats);
   return ((a.nx * a.ny * a.nz + blk - 1) / blk + 7) / 8 * 8;
 }
 
@@ -754,11 +774,18 @@ hipError_t launch_batch_step(int storage, bool odd, int rounds, bool all_ghost_e
   if (tile != 128 && tile != 256) return hipErrorInvalidConfiguration;
   if (stats && !b.partials) return hipErrorInvalidValue;
   const dim3 g(grid), blk(tile);
-#define RFLBM_BATCH_ST(S, O, R, G)                                                             \
+  const bool nt = storage == kF32 && !odd && b.pop_bytes > kStreamBytes;
+#define RFLBM_BATCH_NT(S, O, R, G, N)                                                          \
   if (stats)                                                                                   \
-    hipLaunchKernelGGL((batch_kernel<S, O, R, G, true>), g, blk, 0, stream, b);                \
+    hipLaunchKernelGGL((batch_kernel<S, O, R, G, true, N>), g, blk, 0, stream, b);             \
   else                                                                                         \
-    hipLaunchKernelGGL((batch_kernel<S, O, R, G, false>), g, blk, 0, stream, b);
+    hipLaunchKernelGGL((batch_kernel<S, O, R, G, false, N>), g, blk, 0, stream, b);
+#define RFLBM_BATCH_ST(S, O, R, G)                                                             \
+  if (nt) {                                                                                    \
+    RFLBM_BATCH_NT(S, O, R, G, (S == kF32 && !O))                                              \
+  } else {                                                                                     \
+    RFLBM_BATCH_NT(S, O, R, G, false)                                                          \
+  }
 #define RFLBM_BATCH_G(S, O, R)                                                                 \
   if (all_ghost_eq) {                                                                          \
     RFLBM_BATCH_ST(S, O, R, true)                                                              \
@@ -788,6 +815,7 @@ hipError_t launch_batch_step(int storage, bool odd, int rounds, bool all_ghost_e
 #undef RFLBM_BATCH_R
 #undef RFLBM_BATCH_G
 #undef RFLBM_BATCH_ST
+#undef RFLBM_BATCH_NT
   return hipGetLastError();
 }
 
