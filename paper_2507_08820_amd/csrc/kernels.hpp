@@ -109,7 +109,12 @@ struct BatchArgs {
   uint32_t partial_pitch;                // doubles between partial columns (>= ntiles)
   double* partials;                      // statistics partials [kNumStats][partial_pitch]
   uint64_t pop_bytes;                    // populations of all replicas
+  uint32_t xcd_ranges;                   // 1: one range of tiles per XCD (the grid a multiple of 8)
 };
+
+// Populations beyond which a box or batch streams from memory: larger than what
+// the memory-side cache keeps from one step to the next (step.hip).
+constexpr uint64_t kStreamBytes = 320ull << 20;
 
 // One step of every replica (persistent grid of `grid` blocks walking the tiles);
 // the Philox step count is *b.step + b.step_offset, and the parity `odd` must

@@ -67,8 +67,7 @@ __device__ __forceinline__ constexpr uint32_t stat_at(uint32_t tid) { return tid
 // holds of them from the last step: us per step with / without NT, FP32,
 // 216 MiB (128^3) 81 / 65, 270 MiB 103 / 84, 338 MiB 126 / 123, 506 MiB
 // 184 / 197, 1.7 GiB (256^3) 599 / 653; BF16 without noise 108 MiB (128^3)
-// 41 / 29, 324 MiB 134 / 137 (FP16), 864 MiB 303 / 328.
-constexpr uint64_t kStreamBytes = 320ull << 20;
+// 41 / 29, 324 MiB 134 / 137 (FP16), 864 MiB 303 / 328 (kStreamBytes).
 
 // Visiting order of the whole-row odd step: groups of 2 rows x 8 planes
 // (measured at 512^3: about 1 % faster than plain row order).
@@ -433,7 +432,12 @@ __global__ void __launch_bounds__(kBlock) batch_kernel(const BatchArgs b) {
   CReps* const reps = (CReps*)(b.reps);
   CU32* const tile_rep = (CU32*)(b.tile_rep);
   const uint32_t step = *(CU32*)(b.step) + b.step_offset;
-  for (uint32_t tile = blockIdx.x; tile < b.ntiles; tile += gridDim.x) {
+  // xcd_ranges: each XCD (blocks b mod 8, the grid a multiple of 8) walks one
+  // range of tiles, else all blocks walk the tiles in turn
+  const uint32_t span = (b.ntiles + 7) >> 3, first = b.xcd_ranges ? (blockIdx.x & 7u) * span : 0u;
+  const uint32_t last = b.xcd_ranges ? min(b.ntiles, first + span) : b.ntiles;
+  const uint32_t stride = b.xcd_ranges ? gridDim.x >> 3 : gridDim.x;
+  for (uint32_t tile = first + (b.xcd_ranges ? blockIdx.x >> 3 : blockIdx.x); tile < last; tile += stride) {
     CReps& r = reps[tile_rep[tile]];
     __attribute__((address_space(4))) const StepArgs& a = r.a;
     const uint32_t n = (tile - r.tile0) * blockDim.x + threadIdx.x;
