@@ -288,7 +288,7 @@ static bool in_waves(const rflbm_lattice* L, const StepArgs& a, bool odd) {
 
 hipError_t lattice_clear(rflbm_lattice* L) {
   // populations (deviation 0 = rest at rho0), flag and accumulators
-  return hipMemsetAsync(L->buf, 0, L->L.scratch_off, L->stream);
+  return hipMemsetAsync(L->buf, 0, L->L.partial_off, L->stream);
 }
 
 void lattice_release(rflbm_lattice* L) {
@@ -701,10 +701,11 @@ static rflbm_status sk_prepare(rflbm_lattice* L) {
   RFLBM_HIP(take(&L->sk_sums, 10 * L->nshells * sizeof(double)));
   RFLBM_HIP(take(&L->sk_counts, L->nshells * sizeof(unsigned long long)));
   if (!L->sk_host)
-    RFLBM_HIP(hipHostMalloc(reinterpret_cast<void**>(&L->sk_host), 2 * L->nshells * sizeof(double), hipHostMallocDefault));
+    RFLBM_HIP(hipHostMalloc(reinterpret_cast<void**>(&L->sk_host), 11 * L->nshells * sizeof(double), hipHostMallocDefault));
   RFLBM_HIP(launch_fill_zero(L->sk_sums, 10 * static_cast<size_t>(L->nshells), L->stream));
   RFLBM_HIP(launch_fill_zero(reinterpret_cast<double*>(L->sk_counts), L->nshells, L->stream));
   RFLBM_HIP(launch_sk_count(L->p.nx, L->p.ny, L->p.nz, L->nshells, L->sk_counts, L->stream));
+  RFLBM_HIP(launch_sk_copy(L->sk_counts, L->nshells, L->sk_host + 10 * static_cast<size_t>(L->nshells), L->stream));
   if (L->sk_own) {
     const std::vector<float2> w = sk_twiddles(L->p);
     RFLBM_HIP(take(&L->sk_twiddle, w.size() * sizeof(float2)));
@@ -735,7 +736,7 @@ rflbm_status rflbm_sk_sample(rflbm_lattice* L) {
   const GatherArgs g = gather_args(L, L->p, L->t);
   if (L->sk_own) {
     RFLBM_HIP(launch_sk(L->p.storage, g, L->sk_twiddle, L->nshells, static_cast<float2*>(L->sk_spec), L->sk_partial,
-                        L->sk_sums, L->stream));
+                        L->sk_sums, L->sk_host, L->stream));
   } else {
     const uint64_t N = nodes(L);
     GatherArgs dev = g;
@@ -747,6 +748,7 @@ rflbm_status rflbm_sk_sample(rflbm_lattice* L) {
       RFLBM_HIP(launch_sk_bin(L->sk_spec, L->p.nx, L->p.ny, L->p.nz, L->nshells, L->sk_sums + f * L->nshells,
                               L->stream));
     }
+    RFLBM_HIP(launch_sk_copy(L->sk_sums, 10 * L->nshells, L->sk_host, L->stream));
   }
   L->sk_samples += 1;
   return RFLBM_OK;
@@ -763,10 +765,10 @@ rflbm_status rflbm_get_sk(rflbm_lattice* L, int32_t field, double* shell_sum, in
     if (shell_count) std::memset(shell_count, 0, nshells * sizeof(int64_t));
     return RFLBM_OK;
   }
-  RFLBM_HIP(launch_sk_read(L->sk_sums + field * L->nshells, L->sk_counts, L->nshells, L->sk_host, L->stream));
   RFLBM_HIP(hipStreamSynchronize(L->stream));
-  if (shell_sum) std::memcpy(shell_sum, L->sk_host, nshells * sizeof(double));
-  if (shell_count) std::memcpy(shell_count, L->sk_host + nshells, nshells * sizeof(int64_t));
+  const size_t ns = static_cast<size_t>(nshells);
+  if (shell_sum) std::memcpy(shell_sum, L->sk_host + field * ns, ns * sizeof(double));
+  if (shell_count) std::memcpy(shell_count, L->sk_host + 10 * ns, ns * sizeof(int64_t));
   return RFLBM_OK;
 }
 

@@ -83,7 +83,7 @@ struct rflbm_lattice {
   double* sk_partial = nullptr;             // 10 sk_blocks nshells
   double* sk_sums = nullptr;                // 10 nshells
   unsigned long long* sk_counts = nullptr;  // nshells, set once (they depend on the box alone)
-  double* sk_host = nullptr;                // 2 nshells, pinned: readback of one field
+  double* sk_host = nullptr;                // pinned: the sums after each sample, then the counts
   int64_t sk_samples = 0;
   int32_t nshells = 0;
 };

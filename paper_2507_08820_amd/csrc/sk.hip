@@ -202,9 +202,12 @@ __global__ void __launch_bounds__(512) sk_shells_kernel(const FftPlan p, const S
 }
 
 // shell_sum[field][shell] += the blocks' partials (4 strided parts, then the parts
-// in order).  Block (64 shells, field), 256 threads.
+// in order), the new sums also into host memory, where the readbacks of a
+// sample's ten fields find them without a launch each.  Block (64 shells,
+// field), 256 threads.
 __global__ void __launch_bounds__(256) sk_reduce_kernel(const double* __restrict__ partial, uint32_t blocks,
-                                                        uint32_t nshells, double* __restrict__ shell_sum) {
+                                                        uint32_t nshells, double* __restrict__ shell_sum,
+                                                        double* __restrict__ host_sum) {
   __shared__ double part[4][64];
   const uint32_t i = threadIdx.x & 63u, q = threadIdx.x >> 6, s = blockIdx.x * 64 + i;
   double acc = 0.0;
@@ -215,8 +218,12 @@ __global__ void __launch_bounds__(256) sk_reduce_kernel(const double* __restrict
   }
   part[q][i] = acc;
   __syncthreads();
-  if (q == 0 && s < nshells)
-    shell_sum[static_cast<size_t>(blockIdx.y) * nshells + s] += part[0][i] + part[1][i] + part[2][i] + part[3][i];
+  if (q == 0 && s < nshells) {
+    const size_t at = static_cast<size_t>(blockIdx.y) * nshells + s;
+    const double sum = shell_sum[at] + (part[0][i] + part[1][i] + part[2][i] + part[3][i]);
+    shell_sum[at] = sum;
+    host_sum[at] = sum;
+  }
 }
 
 // Wavevectors per shell.
@@ -241,14 +248,10 @@ __global__ void __launch_bounds__(256) sk_count_kernel(uint32_t nx, uint32_t ny,
     if (cnt[s]) atomicAdd(&shell_count[s], cnt[s]);
 }
 
-// One field's sums and the counts into host memory the GPU can write.
-__global__ void __launch_bounds__(256) sk_read_kernel(const double* __restrict__ sums,
-                                                      const unsigned long long* __restrict__ counts,
-                                                      uint32_t nshells, double* __restrict__ out) {
-  for (uint32_t s = threadIdx.x; s < nshells; s += blockDim.x) {
-    out[s] = sums[s];
-    out[nshells + s] = __longlong_as_double(static_cast<long long>(counts[s]));
-  }
+// Copies n 8-byte words (into host memory that the GPU can write).
+__global__ void __launch_bounds__(256) sk_copy_kernel(const unsigned long long* __restrict__ src, uint32_t n,
+                                                      unsigned long long* __restrict__ dst) {
+  for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) dst[i] = src[i];
 }
 
 __global__ void sk_bin_kernel(const float2* __restrict__ spec, uint32_t nx, uint32_t ny, uint32_t nz,
@@ -320,7 +323,7 @@ uint32_t sk_blocks(uint32_t nx, uint32_t ny, uint32_t nz) {
 }
 
 hipError_t launch_sk(int storage, const GatherArgs& g, const float2* twiddle, uint32_t nshells, float2* spec,
-                     double* partial, double* shell_sum, hipStream_t s) {
+                     double* partial, double* shell_sum, double* host_sum, hipStream_t s) {
   if (!sk_fits(g.nx, g.ny, g.nz)) return hipErrorInvalidValue;
   const uint32_t hx = g.nx / 2 + 1;
   const uint64_t pitch = static_cast<uint64_t>(hx) * g.ny * g.nz;
@@ -375,7 +378,7 @@ hipError_t launch_sk(int storage, const GatherArgs& g, const float2* twiddle, ui
                        static_cast<const float2*>(spec), partial);
   });
   hipLaunchKernelGGL(sk_reduce_kernel, dim3((nshells + 63) / 64, 10), dim3(256), 0, s,
-                     static_cast<const double*>(partial), blocks, nshells, shell_sum);
+                     static_cast<const double*>(partial), blocks, nshells, shell_sum, host_sum);
   return hipGetLastError();
 }
 
@@ -387,9 +390,9 @@ hipError_t launch_sk_count(uint32_t nx, uint32_t ny, uint32_t nz, uint32_t nshel
   return hipGetLastError();
 }
 
-hipError_t launch_sk_read(const double* sums, const unsigned long long* counts, uint32_t nshells, double* out,
-                          hipStream_t s) {
-  hipLaunchKernelGGL(sk_read_kernel, dim3(1), dim3(256), 0, s, sums, counts, nshells, out);
+hipError_t launch_sk_copy(const void* src, uint32_t n, void* dst, hipStream_t s) {
+  hipLaunchKernelGGL(sk_copy_kernel, dim3((n + 255) / 256), dim3(256), 0, s,
+                     static_cast<const unsigned long long*>(src), n, static_cast<unsigned long long*>(dst));
   return hipGetLastError();
 }
 

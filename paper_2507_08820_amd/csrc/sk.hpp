@@ -33,17 +33,17 @@ struct SkTiles {
 bool sk_fits(uint32_t nx, uint32_t ny, uint32_t nz);
 // Blocks per field of the last pass: partial holds 10 sk_blocks nshells doubles.
 uint32_t sk_blocks(uint32_t nx, uint32_t ny, uint32_t nz);
-// Adds |F|^2 / N of the ten fields of the state g to shell_sum[10][nshells].
+// Adds |F|^2 / N of the ten fields of the state g to shell_sum[10][nshells] and
+// writes the new sums to host_sum (pinned host memory) too.
 // twiddle: exp(-2 pi i t / n) for the sides nx, ny, nz one after another; spec:
 // 10 (nx / 2 + 1) ny nz complex values of scratch.
 hipError_t launch_sk(int storage, const GatherArgs& g, const float2* twiddle, uint32_t nshells, float2* spec,
-                     double* partial, double* shell_sum, hipStream_t s);
+                     double* partial, double* shell_sum, double* host_sum, hipStream_t s);
 // Adds the wavevectors per shell to shell_count.
 hipError_t launch_sk_count(uint32_t nx, uint32_t ny, uint32_t nz, uint32_t nshells, unsigned long long* shell_count,
                            hipStream_t s);
-// out[0..nshells) = sums, out[nshells..2 nshells) = counts (as bits).
-hipError_t launch_sk_read(const double* sums, const unsigned long long* counts, uint32_t nshells, double* out,
-                          hipStream_t s);
+// Copies n 8-byte words, in stream order.
+hipError_t launch_sk_copy(const void* src, uint32_t n, void* dst, hipStream_t s);
 // Shell sums of one field's stored spectrum.
 hipError_t launch_sk_bin(const void* spec, uint32_t nx, uint32_t ny, uint32_t nz, uint32_t nshells,
                          double* shell_sum, hipStream_t s);
