@@ -25,7 +25,7 @@
 // values move between lanes so that every access covers whole cache lines),
 // step_flat_kernel (consecutive nodes, for rows that do not fill waves) and
 // batch_kernel (many boxes, persistent grid over tiles of consecutive
-// nodes).  The four one-box kernels take GEQ (every omega_g = 1) as a template
+// nodes).  The four one-box kernels take the ghosts' relaxation as a template
 // parameter, and so does the batch kernel when every replica has it (else it
 // reads the setting per replica).
 #include <hip/hip_runtime.h>
@@ -45,6 +45,13 @@ uint64_t pop_span(const StepArgs& a) { return static_cast<uint64_t>(a.nz >> a.bz
 namespace {
 
 constexpr int kBlock = 256;
+
+// How a kernel's ghost modes relax: their projected non-equilibrium, nothing to
+// relax (every omega_g = 1), or the part rebuilt by the recursion.  The last
+// is a kernel of its own, for compiled into one with the first it cost BGK and
+// general rates 8 registers (85 -> 77, 5 -> 6 waves a SIMD: BGK 256^3 FP16 354 ->
+// 345 us a step, 128^3 FP16 41.9 -> 40.9, 130 x 50 x 70 BF16 12.6 -> 12.45).
+enum Ghosts : int { kGhostsProjected = 0, kGhostsEq = 1, kGhostsRec = 2 };
 
 // Staged statistics, one LDS row per column: node `tid` at stat_at(tid).  The gap
 // after every 32 puts the values that the summing threads (8 parts of 32 nodes
@@ -229,7 +236,7 @@ __device__ __forceinline__ void block_stats(const float (*stat_lds)[kStatPitch],
 
 // One box: a block covers bx x by nodes of one z plane (blockDim = (bx, by));
 // blocks of one row (by = 1) take the rows in memory order, others plane by plane.
-template <int S, bool ODD, int ROUNDS, bool STATS, bool GEQ>
+template <int S, bool ODD, int ROUNDS, bool STATS, int GHOSTS>
 __global__ void __launch_bounds__(kBlock) step_kernel(const StepArgs a) {
   uint32_t tile = blockIdx.x;
   if (a.xcd_remap) tile = (tile & 7u) * (gridDim.x >> 3) + (tile >> 3);
@@ -257,7 +264,7 @@ __global__ void __launch_bounds__(kBlock) step_kernel(const StepArgs a) {
     constexpr bool BUFFER_ACCESS = true;
     constexpr bool BRICKS = true;
     constexpr bool ROW_SHIFT = false;
-    constexpr bool GHOST_EQ = GEQ, NT = true;
+    constexpr bool GHOST_REC = GHOSTS == kGhostsRec, GHOST_EQ = GHOSTS == kGhostsEq, NT = true;
     [[maybe_unused]] uint32_t (*row_edge_in)[kMaxRowWaves] = nullptr;
     [[maybe_unused]] uint32_t (*row_edge_out)[kMaxRowWaves] = nullptr;
 #include "node_body.inc"
@@ -280,7 +287,7 @@ __global__ void __launch_bounds__(kBlock) step_kernel(const StepArgs a) {
 // 5.0; large boxes do not care, except with statistics, whose staging and
 // partials weigh more (us per step in blocks of 64 / 256: 16^3 5.3 / 6.1, 17 x 19
 // x 23 5.4 / 6.6, 48^3 FP16 11.8 / 8.1, 100^3 49 / 40; flat_block).
-template <int S, bool ODD, int ROUNDS, bool STATS, bool GEQ, int BLOCK>
+template <int S, bool ODD, int ROUNDS, bool STATS, int GHOSTS, int BLOCK>
 __global__ void __launch_bounds__(BLOCK) step_flat_kernel(const StepArgs a) {
   uint32_t tile = blockIdx.x;
   if (a.xcd_remap) tile = (tile & 7u) * (gridDim.x >> 3) + (tile >> 3);
@@ -299,7 +306,7 @@ __global__ void __launch_bounds__(BLOCK) step_flat_kernel(const StepArgs a) {
     constexpr bool BUFFER_ACCESS = true;
     constexpr bool BRICKS = true;
     constexpr bool ROW_SHIFT = false;
-    constexpr bool GHOST_EQ = GEQ;
+    constexpr bool GHOST_REC = GHOSTS == kGhostsRec, GHOST_EQ = GHOSTS == kGhostsEq;
     constexpr bool NT = false;
     [[maybe_unused]] uint32_t (*row_edge_in)[kMaxRowWaves] = nullptr;
     [[maybe_unused]] uint32_t (*row_edge_out)[kMaxRowWaves] = nullptr;
@@ -314,11 +321,11 @@ __global__ void __launch_bounds__(BLOCK) step_flat_kernel(const StepArgs a) {
 // Step without statistics in one-wave blocks: block b covers the 64
 // nodes x = 64 (b mod (nx / 64)) + lane of x-row b / (nx / 64) of the memory
 // order (brick_row; nx a multiple of 64).
-template <int S, int ROUNDS, bool GEQ, bool ODD, bool NT>
+template <int S, int ROUNDS, int GHOSTS, bool ODD, bool NT>
 __global__ void __launch_bounds__(64) step_wave_kernel(const StepArgs a) {
   constexpr bool STATS = false, SMALL_BOX = false, ROW_SHIFT = false, BUFFER_ACCESS = true;
   constexpr bool BRICKS = true;
-  constexpr bool GHOST_EQ = GEQ, STATS_WAVE = false;
+  constexpr bool GHOST_REC = GHOSTS == kGhostsRec, GHOST_EQ = GHOSTS == kGhostsEq, STATS_WAVE = false;
   [[maybe_unused]] float (*stat_lds)[kStatPitch] = nullptr;
   [[maybe_unused]] float (*stat_wave)[kMaxRowWaves] = nullptr;
   [[maybe_unused]] const uint32_t tid = 0;
@@ -344,10 +351,10 @@ __global__ void __launch_bounds__(64) step_wave_kernel(const StepArgs a) {
 // nodes' statistics, and the block adds its waves' sums in FP64 (fixed order)
 // into one partial per block, as step_kernel does; the even step takes this
 // kernel only for statistics (one partial per row instead of one per wave).
-template <int S, int ROUNDS, bool GEQ, bool STATS, bool ODD, bool NT>
+template <int S, int ROUNDS, int GHOSTS, bool STATS, bool ODD, bool NT>
 __global__ void __launch_bounds__(kMaxRowWaves * 64) step_row_kernel(const StepArgs a) {
   constexpr bool SMALL_BOX = false, ROW_SHIFT = ODD, BUFFER_ACCESS = true, BRICKS = true;
-  constexpr bool GHOST_EQ = GEQ, STATS_WAVE = true;
+  constexpr bool GHOST_REC = GHOSTS == kGhostsRec, GHOST_EQ = GHOSTS == kGhostsEq, STATS_WAVE = true;
   [[maybe_unused]] float (*stat_lds)[kStatPitch] = nullptr;
   [[maybe_unused]] const uint32_t tid = 0;
   __shared__ uint32_t row_edge_in[18][kMaxRowWaves];   // gather (stored words)
@@ -402,7 +409,7 @@ __global__ void __launch_bounds__(kMaxRowWaves * 64) step_row_kernel(const StepA
 // Philox counter) is the device counter plus b.step_offset, so that a captured
 // graph of several steps (offsets 0, 1, ...) can be replayed from any t; the
 // parity is a template parameter, and the host only replays graphs of an even
-// number of steps from an even step count.  GEQ: every replica has every
+// number of steps from an even step count.  kGhostsEq: every replica has every
 // omega_g = 1; otherwise each replica's own setting is read at run time.
 // NT: even steps of FP32 batches beyond the memory-side cache (64 replicas of
 // 32^3..96^3, 2.3 GB: 826 us a step, 905 without); the rows of 16-bit replicas
@@ -410,7 +417,7 @@ __global__ void __launch_bounds__(kMaxRowWaves * 64) step_row_kernel(const StepA
 // in the cache (24 of 8^3..32^3, FP32: 17.0 with, 13.4 without).
 // STATS: each tile's statistics are reduced in the block (fixed order, FP64)
 // into column t of b.partials, for batch_stats_reduce.
-template <int S, bool ODD, int ROUNDS, bool GEQ, bool STATS, bool NT>
+template <int S, bool ODD, int ROUNDS, int GHOSTS, bool STATS, bool NT>
 __global__ void __launch_bounds__(kBlock) batch_kernel(const BatchArgs b) {
   constexpr bool STATS_WAVE = false;
   [[maybe_unused]] float (*stat_wave)[kMaxRowWaves] = nullptr;
@@ -446,7 +453,8 @@ __global__ void __launch_bounds__(kBlock) batch_kernel(const BatchArgs b) {
       const uint32_t rem = n - z * (a.nx * a.ny);
       const uint32_t y = fast_div(rem, FastDiv{r.div_x.m, r.div_x.s});
       const uint32_t x = rem - y * a.nx;
-      const bool GHOST_EQ = GEQ || a.ghost_eq != 0u;
+      const bool GHOST_EQ = GHOSTS == kGhostsEq || a.ghost_eq != 0u;
+      const bool GHOST_REC = a.ghost_rec != 0u;
 #include "node_body.inc"
     } else if constexpr (STATS) {
 #pragma unroll
@@ -580,12 +588,19 @@ __global__ void __launch_bounds__(256) fold_stats(const double* partials, uint32
   }
 }
 
+// Calls f(integral_constant<int, kGhosts...>) for the lattice's ghosts.
+template <class F>
+void by_ghosts(const StepArgs& a, F f) {
+  if (a.ghost_eq) f(std::integral_constant<int, kGhostsEq>{});
+  else if (a.ghost_rec) f(std::integral_constant<int, kGhostsRec>{});
+  else f(std::integral_constant<int, kGhostsProjected>{});
+}
+
 template <int S, bool ODD, int R, bool ST>
 hipError_t launch_t(const StepArgs& a, const Launch& l, hipStream_t s) {
-  if (a.ghost_eq)
-    hipLaunchKernelGGL((step_kernel<S, ODD, R, ST, true>), dim3(l.grid), dim3(l.bx, l.by), 0, s, a);
-  else
-    hipLaunchKernelGGL((step_kernel<S, ODD, R, ST, false>), dim3(l.grid), dim3(l.bx, l.by), 0, s, a);
+  by_ghosts(a, [&](auto gh) {
+    hipLaunchKernelGGL((step_kernel<S, ODD, R, ST, decltype(gh)::value>), dim3(l.grid), dim3(l.bx, l.by), 0, s, a);
+  });
   return hipGetLastError();
 }
 
@@ -596,8 +611,9 @@ uint32_t flat_block(const StepArgs& a, bool stats) {
 
 template <int S, bool ODD, int R, bool ST, int BLOCK>
 void launch_flat_b(const StepArgs& a, uint32_t grid, hipStream_t s) {
-  if (a.ghost_eq) hipLaunchKernelGGL((step_flat_kernel<S, ODD, R, ST, true, BLOCK>), dim3(grid), dim3(BLOCK), 0, s, a);
-  else hipLaunchKernelGGL((step_flat_kernel<S, ODD, R, ST, false, BLOCK>), dim3(grid), dim3(BLOCK), 0, s, a);
+  by_ghosts(a, [&](auto gh) {
+    hipLaunchKernelGGL((step_flat_kernel<S, ODD, R, ST, decltype(gh)::value, BLOCK>), dim3(grid), dim3(BLOCK), 0, s, a);
+  });
 }
 
 template <int S, bool ODD, int R, bool ST>
@@ -627,14 +643,16 @@ hipError_t launch_flat_s(bool odd, int rounds, bool stats, const StepArgs& a, ui
 
 template <int S, int R, bool ST, bool ODD, bool NT>
 void launch_row_g(const StepArgs& a, dim3 g, dim3 blk, hipStream_t s) {
-  if (a.ghost_eq) hipLaunchKernelGGL((step_row_kernel<S, R, true, ST, ODD, NT>), g, blk, 0, s, a);
-  else hipLaunchKernelGGL((step_row_kernel<S, R, false, ST, ODD, NT>), g, blk, 0, s, a);
+  by_ghosts(a, [&](auto gh) {
+    hipLaunchKernelGGL((step_row_kernel<S, R, decltype(gh)::value, ST, ODD, NT>), g, blk, 0, s, a);
+  });
 }
 
 template <int S, int R, bool ODD, bool NT>
 void launch_wave_g(const StepArgs& a, dim3 g, hipStream_t s) {
-  if (a.ghost_eq) hipLaunchKernelGGL((step_wave_kernel<S, R, true, ODD, NT>), g, dim3(64), 0, s, a);
-  else hipLaunchKernelGGL((step_wave_kernel<S, R, false, ODD, NT>), g, dim3(64), 0, s, a);
+  by_ghosts(a, [&](auto gh) {
+    hipLaunchKernelGGL((step_wave_kernel<S, R, decltype(gh)::value, ODD, NT>), g, dim3(64), 0, s, a);
+  });
 }
 
 template <int S, bool ODD, bool ST>
@@ -792,9 +810,9 @@ hipError_t launch_batch_step(int storage, bool odd, int rounds, bool all_ghost_e
   }
 #define RFLBM_BATCH_G(S, O, R)                                                                 \
   if (all_ghost_eq) {                                                                          \
-    RFLBM_BATCH_ST(S, O, R, true)                                                              \
+    RFLBM_BATCH_ST(S, O, R, kGhostsEq)                                                              \
   } else {                                                                                     \
-    RFLBM_BATCH_ST(S, O, R, false)                                                             \
+    RFLBM_BATCH_ST(S, O, R, kGhostsRec)                                                             \
   }
 #define RFLBM_BATCH_R(S, O)                                                                    \
   switch (rounds) {                                                                            \
