@@ -202,6 +202,7 @@ StepArgs step_args(const rflbm_lattice* L) {
   a.by_log = L->L.by_log;
   a.bz_log = L->L.bz_log;
   a.plane_pitch = L->L.plane_pitch;
+  a.turn_bytes = L->turn_bytes;
   a.tiles_x = (p.nx + L->launch.bx - 1) / L->launch.bx;
   a.tiles_y = (p.ny + L->launch.by - 1) / L->launch.by;
   a.ntiles = a.tiles_x * a.tiles_y * static_cast<uint32_t>(p.nz);
@@ -251,6 +252,7 @@ StepArgs step_args(const rflbm_lattice* L) {
 void lattice_init(rflbm_lattice* L, const rflbm_params& p, uint8_t* buf, hipStream_t s, bool bricks) {
   L->p = p;
   L->L = layout_for(p, bricks);
+  L->turn_bytes = L->L.pop_bytes;
   L->buf = buf;
   L->stream = s;
   if (hipGetDevice(&L->device) != hipSuccess) {

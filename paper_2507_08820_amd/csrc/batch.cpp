@@ -361,6 +361,7 @@ rflbm_status rflbm_batch_create(int32_t n, const rflbm_params* p, void* dev_buf,
       return fail(RFLBM_EHIP, "clearing a replica failed");
     }
   }
+  for (rflbm_lattice* v : b->views) v->turn_bytes = b->pop_bytes;
   if (launch_fill_zero(reinterpret_cast<double*>(b->buf + B.step_off), 1, b->stream) != hipSuccess) {
     rflbm_batch_destroy(b);
     return fail(RFLBM_EHIP, "clearing the step counter failed");

@@ -61,6 +61,7 @@ struct rflbm_lattice {
   rflbm::Layout L;
   uint8_t* buf = nullptr;
   bool owns_buf = false;
+  uint64_t turn_bytes = 0;  // populations stepped in turn with these, and these
   bool is_view = false;  // a replica of a batch (borrowed, destroyed with the batch)
   hipStream_t stream = nullptr;
   int device = 0;  // HIP device current when the lattice was set up
@@ -68,9 +69,7 @@ struct rflbm_lattice {
   int32_t stats_every = 0;
   rflbm::Launch launch{};
   bool xcd_remap = true;
-  // row-aligned blocks for steps without statistics (on by default), used
-  // where the step is bandwidth bound (FP32 storage, or k_BT = 0): even steps
-  // in one-wave x-segments, odd steps in whole-row blocks when nx fits
+  // blocks that follow the x-rows (rflbm_set_row_blocks); off: tiles only
   bool row_mode = true;
   // S(k) state (library-allocated on first use)
   bool sk_ready = false;

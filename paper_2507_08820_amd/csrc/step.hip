@@ -716,7 +716,7 @@ hipError_t launch_row_p(bool odd, bool stats, int rounds, const StepArgs& a, uin
 
 }  // namespace
 
-bool streams(const StepArgs& a) { return pop_span(a) > kStreamBytes; }
+bool streams(const StepArgs& a) { return a.turn_bytes > kStreamBytes; }
 
 hipError_t launch_step_wave(int storage, bool odd, int rounds, const StepArgs& a, hipStream_t stream) {
   if (a.nx % 64 != 0 || a.nx == 0) return hipErrorInvalidConfiguration;
