@@ -9,7 +9,7 @@
 //
 // Sides up to 1024 (and see below): three passes over the data.
 //   sk_rows_kernel: moments of whole x-rows and their transforms along x, two
-//     real fields to one complex line, so no field is stored in real space;
+//     rows of a field to one complex line, so no field is stored in real space;
 //   sk_columns_kernel: along y, in place;
 //   sk_shells_kernel: along z, and straight from LDS into shell sums, so the
 //     transforms are not written again.
@@ -37,10 +37,7 @@ namespace rflbm {
 
 namespace {
 
-constexpr int kPairs = 5;  // complex lines of a row: two fields each
-// Moment fields (order of the interface) carried by pair p: fields of like size,
-// since each sees the rounding of the other.
-__device__ constexpr int kPairA[kPairs] = {0, 1, 4, 6, 8}, kPairB[kPairs] = {3, 2, 5, 7, 9};
+constexpr int kHalf = 5;  // fields transformed together: half of the ten
 
 // Shell round(sqrt(k2)), exact: s with s (s - 1) < k2 <= s (s + 1).
 __device__ __forceinline__ uint32_t shell_of(uint32_t k2) {
@@ -56,49 +53,72 @@ __device__ __forceinline__ uint32_t wave2(uint32_t k, uint32_t n) {
   return a * a;
 }
 
-// Blocks of `rows` x-rows (plane order).  The row's ten fields become five
-// complex lines; transform c of fields (a, b) splits as a = (c(k) + c*(-k)) / 2,
-// b = (c(k) - c*(-k)) / 2i.
+// Blocks of `pairs` pairs of x-rows (plane order).  A thread forms the moments of
+// its node in both rows of a pair; each field of the pair is one complex line,
+// five fields at a time, and its transform c splits as a = (c(k) + c*(-k)) / 2,
+// b = (c(k) - c*(-k)) / 2i into those of the two rows.  Two rows of one field and
+// not two fields: the smaller part of a line takes the rounding of the larger,
+// and fields may differ by any factor (a flow without noise).  Two fields to a line,
+// one of them 1e-4 (1e-6) of the other, had shell sums 2e-4 (2e-2) off, against
+// 2e-7 for rows (64^3), and a field that overflowed took its partner with it.
 template <int S, bool ODD, int KIND>
 __global__ void __launch_bounds__(1024) sk_rows_kernel(const GatherArgs g, const FftPlan p, const SkRows r,
                                                        float2* __restrict__ spec) {
   using C = Codec<S>;
   using T = typename C::T;
   extern __shared__ float2 sh[];
-  const uint32_t nx = g.nx, lines = kPairs * r.rows;
+  const uint32_t nx = g.nx, lines = kHalf * r.pairs;
   float2* const lds = sh;
   float2* const tw = sh + static_cast<size_t>(nx) * lines;
   const uint32_t tid = threadIdx.x;
   for (uint32_t t = tid; t < nx; t += blockDim.x) tw[t] = p.twiddle[t];
-  const uint32_t total = g.ny * g.nz, row0 = blockIdx.x * r.rows;
-  const uint32_t rows = min(r.rows, total - row0);
-  if (tid < rows * nx) {
-    const uint32_t q = fast_div(tid, g.div_x);
-    NodeXYZ c;
-    c.x = tid - q * nx;
-    c.z = fast_div(row0 + q, g.div_y);
-    c.y = row0 + q - c.z * g.ny;
-    const Slots<ODD> slot(c, g);
-    const T* pop = static_cast<const T*>(g.pop);
-    float v[kQ];
+  const uint32_t total = g.ny * g.nz, row0 = blockIdx.x * 2 * r.pairs;
+  const uint32_t pairs = min(r.pairs, (total - row0 + 1) >> 1);
+  const uint32_t q = fast_div(tid, g.div_x), x = tid - q * nx;
+  float f[2][2 * kHalf];  // the node's fields in the two rows (no second row: 0)
+  if (q < pairs) {
 #pragma unroll
-    for (int i = 0; i < kQ; ++i) v[i] = C::decode(pop[slot(i)], g.sigma[speed_class(i)]);
-    forward27(v);
-    // rho - rho0 instead of rho: the mean does not enter n != 0
-    const float f[10] = {v[0], v[1], v[3], v[9], v[mode_slot(4)], v[mode_slot(5)], v[mode_slot(6)], v[mode_slot(7)],
-                         v[mode_slot(8)], v[mode_slot(9)]};
+    for (int h = 0; h < 2; ++h) {
+      const uint32_t row = row0 + 2 * q + h;
+      if (row < total) {
+        NodeXYZ c;
+        c.x = x;
+        c.z = fast_div(row, g.div_y);
+        c.y = row - c.z * g.ny;
+        const Slots<ODD> slot(c, g);
+        const T* pop = static_cast<const T*>(g.pop);
+        float v[kQ];
 #pragma unroll
-    for (int k = 0; k < kPairs; ++k) lds[c.x * lines + q * kPairs + k] = make_float2(f[kPairA[k]], f[kPairB[k]]);
+        for (int i = 0; i < kQ; ++i) v[i] = C::decode(pop[slot(i)], g.sigma[speed_class(i)]);
+        forward27(v);
+        // rho - rho0 instead of rho: the mean does not enter n != 0
+#pragma unroll
+        for (int k = 0; k < 2 * kHalf; ++k) f[h][k] = v[mode_slot(k)];
+      } else {
+#pragma unroll
+        for (int k = 0; k < 2 * kHalf; ++k) f[h][k] = 0.0f;
+      }
+    }
   }
-  fft_lines<KIND>(lds, tw, lines, r.div_lines, p, tid, blockDim.x);
   const uint32_t hx = nx / 2 + 1;
-  for (uint32_t e = tid; e < rows * kPairs * hx; e += blockDim.x) {
-    const uint32_t l = fast_div(e, r.div_hx), k = e - l * hx;
-    const uint32_t q = l / kPairs, pair = l - q * kPairs;
-    const float2 c = lds[k * lines + l], d = lds[(k == 0 ? 0 : nx - k) * lines + l];
-    const uint64_t at = static_cast<uint64_t>(row0 + q) * hx + k;
-    spec[kPairA[pair] * r.pitch + at] = make_float2(0.5f * (c.x + d.x), 0.5f * (c.y - d.y));
-    spec[kPairB[pair] * r.pitch + at] = make_float2(0.5f * (c.y + d.y), 0.5f * (d.x - c.x));
+#pragma unroll
+  for (int half = 0; half < 2; ++half) {
+    if (q < pairs) {
+#pragma unroll
+      for (int k = 0; k < kHalf; ++k)
+        lds[x * lines + q * kHalf + k] = make_float2(f[0][half * kHalf + k], f[1][half * kHalf + k]);
+    }
+    fft_lines<KIND>(lds, tw, lines, r.div_lines, p, tid, blockDim.x);
+    for (uint32_t e = tid; e < pairs * kHalf * hx; e += blockDim.x) {
+      const uint32_t l = fast_div(e, r.div_hx), k = e - l * hx;
+      const uint32_t pair = l / kHalf, field = half * kHalf + l - pair * kHalf;
+      const float2 c = lds[k * lines + l], d = lds[(k == 0 ? 0 : nx - k) * lines + l];
+      const uint32_t row = row0 + 2 * pair;
+      float2* const at = spec + field * r.pitch + static_cast<uint64_t>(row) * hx + k;
+      at[0] = make_float2(0.5f * (c.x + d.x), 0.5f * (c.y - d.y));
+      if (row + 1 < total) at[hx] = make_float2(0.5f * (c.y + d.y), 0.5f * (d.x - c.x));
+    }
+    if (half == 0) __syncthreads();  // the lines are written again
   }
 }
 
@@ -332,13 +352,13 @@ hipError_t launch_sk(int storage, const GatherArgs& g, const float2* twiddle, ui
   py.twiddle = twiddle + g.nx;
   pz.twiddle = twiddle + g.nx + g.ny;
   SkRows r{};
-  r.rows = g.nx >= 256 ? 1 : 256 / g.nx;
+  r.pairs = g.nx >= 256 ? 1 : 256 / g.nx;
   r.pitch = pitch;
-  r.div_lines = make_fastdiv(kPairs * r.rows);
+  r.div_lines = make_fastdiv(kHalf * r.pairs);
   r.div_hx = make_fastdiv(hx);
-  const uint32_t rows = g.ny * g.nz, row_threads = (r.rows * g.nx + 63) / 64 * 64;
-  const size_t row_lds = sizeof(float2) * (static_cast<size_t>(g.nx) * kPairs * r.rows + g.nx);
-  const dim3 row_grid((rows + r.rows - 1) / r.rows), row_block(row_threads);
+  const uint32_t rows = g.ny * g.nz, row_threads = (r.pairs * g.nx + 63) / 64 * 64;
+  const size_t row_lds = sizeof(float2) * (static_cast<size_t>(g.nx) * kHalf * r.pairs + g.nx);
+  const dim3 row_grid((rows + 2 * r.pairs - 1) / (2 * r.pairs)), row_block(row_threads);
   const auto with_kind = [](const FftPlan& p, auto f) {
     switch (fft_kind(p)) {
       case kFftPow2: f(std::integral_constant<int, kFftPow2>{}); break;

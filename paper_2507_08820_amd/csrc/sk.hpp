@@ -11,9 +11,9 @@ namespace rflbm {
 // one round of the two such blocks a CU holds.
 constexpr uint32_t kSkBlocks = 51;
 
-// The pass along x: rows per block, values of one field's spectrum.
+// The pass along x: pairs of rows per block, values of one field's spectrum.
 struct SkRows {
-  uint32_t rows;
+  uint32_t pairs;
   uint64_t pitch;
   FastDiv div_lines;  // division by the complex lines of a block
   FastDiv div_hx;     // division by nx / 2 + 1
