@@ -15,12 +15,12 @@
 #include <hip/hip_runtime.h>
 
 #include "fastdiv.hpp"
+#include "policy.hpp"
 
 namespace rflbm {
 
 constexpr int kFftMaxPasses = 12;
 constexpr int kFftPerThread = 8;      // values a thread holds in a pass
-constexpr uint32_t kFftMaxLength = 1024;
 
 struct FftPlan {
   uint32_t n;

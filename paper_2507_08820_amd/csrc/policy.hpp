@@ -1,0 +1,53 @@
+// policy.hpp -- which kernel a call takes, as rules on sizes alone: plain host code
+// without HIP, so that the rules can be checked where there is no GPU.
+#pragma once
+#include <cstdint>
+
+namespace rflbm {
+
+constexpr uint32_t kFftMaxLength = 1024;  // of the transforms in LDS (fft.hpp)
+
+// Largest prime factor of n >= 2.
+inline uint32_t largest_prime(uint32_t n) {
+  uint32_t p = 1;
+  for (uint32_t d = 2; n > 1; ++d)
+    for (; n % d == 0; n /= d) p = d;
+  return p;
+}
+
+// True when the transforms in LDS take the box, else hipFFT.  A factor above 7
+// costs them r operations a value where hipFFT has radices up to 17 and goes
+// another way beyond.  ms of a snapshot, in LDS / hipFFT:
+//  - one long prime side costs most along z and least along x, where hipFFT is
+//    slowest: 32 x 32 x 1021 2.1 / 0.56, 45 x 45 x 331 0.72 / 0.60, 26 x 199 x 199
+//    0.94 / 0.78, 32 x 1021 x 32 1.25 / 0.61, 1021 x 32 x 32 1.86 / 0.99; but 72 x 72 x
+//    199 0.62 / 0.64, 32 x 509 x 32 0.42 / 0.45, 509 x 45 x 45 0.93 / 1.2; in a
+//    few x-rows the launches weigh more: 8 x 8 x 509 0.19 / 0.30, 1021 x 2 x 2 0.86 / 0.39;
+//  - beyond 2^20 nodes no prime above 64 (137 x 149 x 151 3.6 / 2.6);
+//  - even nx, factors 11, 13, 17: 238^3 2.0 / 2.6, 242^3 2.6 / 2.6, 260^3 4.3 / 2.9,
+//    286^3 7.9 / 3.8, 286 x 256 x 256 3.0 / 2.3, 256 x 256 x 286 3.1 / 3.0; such a side
+//    along y alone is no loss (256 x 286 x 256 2.4 / 3.0), nor is odd nx (255^3
+//    2.4 / 5.4, 363^3 12.0 / 15.7);
+//  - even nx, factors of 19 to 61: 222^3 3.0 / 3.5, 212^3 3.2 / 3.3, 236^3 4.3 / 4.0,
+//    244^3 4.7 / 4.1, 344^3 14.4 / 13.0, 366^3 22 / 15; but 290^3 8.3 / 8.6, 348^3
+//    11.7 / 13.4, 406^3 16 / 20.
+inline bool sk_fits(uint32_t nx, uint32_t ny, uint32_t nz) {
+  if (nx > kFftMaxLength || ny > kFftMaxLength || nz > kFftMaxLength) return false;
+  const auto factor = [](uint32_t n) {  // 0: radices of the transforms in LDS alone
+    const uint32_t p = largest_prime(n);
+    return p > 7 ? p : 0u;
+  };
+  const uint32_t rx = factor(nx), ry = factor(ny), rz = factor(nz);
+  const uint32_t sum = rx + ry + rz, most = rx > ry ? (rx > rz ? rx : rz) : (ry > rz ? ry : rz);
+  const uint64_t nodes = static_cast<uint64_t>(nx) * ny * nz;
+  if (sum == 0) return true;
+  if (nodes <= (1u << 17)) return rx <= 400 && rz <= 600;
+  if (rx / 560.0 + ry / 510.0 + rz / 250.0 > 1.0) return false;
+  if (nodes <= (1u << 20)) return true;
+  if (most > 64) return false;
+  if (nx % 2 != 0) return true;
+  if (most <= 17) return nodes <= 27ull << 19 || sum == ry;
+  return sum <= 100 || nodes * sum <= 1800000000ull;
+}
+
+}  // namespace rflbm

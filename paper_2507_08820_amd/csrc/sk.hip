@@ -20,10 +20,8 @@
 // transform and one binning kernel per field (43 launches): 256^3 FP32 1.14 / 2.64
 // ms, 128^3 FP16 0.12 / 0.79, 64^3 0.031 / 0.22, 16^3 0.020 / 0.12, 200 x 320 x
 // 180 BF16 0.87 / 2.2.
-// The other way stays for sides beyond 1024 (LDS), and for boxes of more than
-// 2^20 nodes with a prime factor above 64, whose sums cost more than hipFFT's
-// transform of such lengths (137 x 149 x 151 3.6 / 2.6 ms, 311 x 97 x 64 2.0 / 1.8;
-// but 101^3 0.74 / 1.37, 67^3 0.22 / 0.75, 251 x 64 x 64 0.55 / 1.05).
+// The other way stays for sides beyond 1024 (LDS), and where the sums of prime
+// factors above 7 cost more than hipFFT's transforms (sk_fits, policy.hpp).
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -323,16 +321,6 @@ SkTiles make_tiles(uint32_t n, uint32_t hx, uint64_t lines, uint64_t pitch) {
 }
 
 }  // namespace
-
-bool sk_fits(uint32_t nx, uint32_t ny, uint32_t nz) {
-  if (nx > kFftMaxLength || ny > kFftMaxLength || nz > kFftMaxLength) return false;
-  uint32_t prime = 1;
-  for (uint32_t n : {nx, ny, nz}) {
-    const FftPlan p = make_fft_plan(n);
-    for (uint32_t k = 0; k < p.passes; ++k) prime = p.radix[k] > prime ? p.radix[k] : prime;
-  }
-  return prime <= 64 || static_cast<uint64_t>(nx) * ny * nz <= (1ull << 20);
-}
 
 uint32_t sk_blocks(uint32_t nx, uint32_t ny, uint32_t nz) {
   const uint32_t hx = nx / 2 + 1;

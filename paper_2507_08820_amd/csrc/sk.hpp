@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include "kernels.hpp"
+#include "policy.hpp"
 
 namespace rflbm {
 
@@ -29,8 +30,6 @@ struct SkTiles {
   FastDiv div_hx, div_tx;
 };
 
-// True when the passes in LDS take the box (else hipFFT).
-bool sk_fits(uint32_t nx, uint32_t ny, uint32_t nz);
 // Blocks per field of the last pass: partial holds 10 sk_blocks nshells doubles.
 uint32_t sk_blocks(uint32_t nx, uint32_t ny, uint32_t nz);
 // Adds |F|^2 / N of the ten fields of the state g to shell_sum[10][nshells] and

@@ -1,0 +1,47 @@
+"""CPU checks of the rules that pick a kernel by size (csrc/policy.hpp, plain host
+code): measured boxes on both sides of each line."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2507_08820_amd", "csrc")
+
+
+@pytest.fixture(scope="module")
+def evaluate(tmp_path_factory):
+    """Values of C++ expressions over policy.hpp, as integers."""
+    tmp = tmp_path_factory.mktemp("policy")
+
+    def run(expressions):
+        src = tmp / "probe.cpp"
+        lines = "\n".join(f'  std::printf("%lld\\n", static_cast<long long>({e}));' for e in expressions)
+        src.write_text(f"#include <cstdio>\n#include \"policy.hpp\"\nusing namespace rflbm;\nint main() {{\n{lines}\n}}\n")
+        exe = tmp / "probe"
+        subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-I", CSRC, str(src), "-o", str(exe)], check=True)
+        return [int(v) for v in subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout.split()]
+
+    return run
+
+
+def test_structure_factor_route(evaluate):
+    """Boxes whose transforms in LDS were faster than hipFFT's, and slower ones."""
+    own = [(2, 2, 2), (256, 256, 256), (512, 512, 512), (1000, 100, 50), (100, 100, 100), (17, 19, 23), (61, 61, 61),
+           (101, 101, 101), (72, 72, 199), (64, 251, 64), (251, 64, 64), (509, 45, 45), (8, 8, 509), (2, 1021, 2),
+           (122, 122, 64), (61, 256, 256), (143, 143, 143), (187, 187, 187), (209, 209, 209), (238, 238, 238),
+           (255, 255, 255), (363, 363, 363), (256, 286, 256), (222, 222, 222), (212, 212, 212), (348, 348, 348),
+           (406, 406, 406), (183, 183, 183), (305, 305, 305)]
+    hipfft = [(1030, 3, 2), (2, 2, 2048), (1021, 2, 2), (509, 8, 8), (1021, 32, 32), (32, 1021, 32), (32, 32, 1021),
+              (45, 45, 331), (45, 45, 509), (2, 1021, 509), (509, 2, 1021), (26, 199, 199), (38, 701, 38),
+              (134, 96, 90), (137, 149, 151), (242, 242, 242), (260, 260, 260), (286, 286, 286), (374, 374, 374),
+              (520, 520, 130), (272, 544, 136), (286, 256, 256), (256, 256, 286), (236, 236, 236), (244, 244, 244),
+              (344, 344, 344), (366, 366, 366), (488, 488, 488)]
+    got = evaluate([f"sk_fits({x}, {y}, {z})" for x, y, z in own + hipfft])
+    assert [d for d, g in zip(own + hipfft, got) if g != (d in own)] == []
+
+
+def test_largest_prime(evaluate):
+    def prime(n):
+        return max(d for d in range(2, n + 1) if n % d == 0 and all(d % k for k in range(2, d)))
+    assert evaluate([f"largest_prime({n})" for n in range(2, 200)]) == [prime(n) for n in range(2, 200)]
