@@ -13,6 +13,7 @@
 #include "d3q27.hpp"
 #include "kernels.hpp"
 #include "philox.hpp"
+#include "policy.hpp"
 #include "slots.hpp"
 #include "storage.hpp"
 
@@ -247,10 +248,7 @@ __global__ void __launch_bounds__(256) init_thermal_kernel(const GatherArgs g, c
 
 // Moment fields of the nodes n0 .. n0 + count - 1: field c of node n0 + k goes
 // to dst[c * pitch + k].
-// NT: populations read past the caches (more than the memory-side cache holds,
-// and each cache line read by one wave only, so not at odd step counts): 192^3
-// FP32 0.197 -> 0.173 ms, 256^3 FP16 0.295 -> 0.253 ms; a box that fits the
-// cache loses by it (130 x 101 x 97 BF16 0.023 -> 0.030 ms).
+// NT: populations read past the caches (read_streams, policy.hpp).
 template <int S, bool ODD, bool NT>
 __global__ void __launch_bounds__(256) moments_kernel(const GatherArgs g, uint32_t mask, uint64_t n0, uint64_t count,
                                                       uint64_t pitch, float* __restrict__ dst) {
@@ -391,9 +389,6 @@ __global__ void __launch_bounds__(256) swap_parity_kernel(const GatherArgs g) {
   }
 }
 
-// Memory-side cache of an MI355X (Infinity Cache): reads of less may stay in it.
-constexpr uint64_t kCacheBytes = 256ull << 20;
-
 uint32_t grid_for(uint64_t work, uint32_t block) {
   const uint64_t g = (work + block - 1) / block;
   return static_cast<uint32_t>(g < 65536 ? (g == 0 ? 1 : g) : 65536);
@@ -478,7 +473,7 @@ hipError_t launch_get_moments_range(int storage, const GatherArgs& g, uint32_t m
   if (count == 0) return hipSuccess;
   const dim3 grid(static_cast<uint32_t>((count + 255) / 256)), block(256);
   const uint64_t pop_bytes = static_cast<uint64_t>(kQ) * g.nx * g.ny * g.nz * storage_bytes(storage);
-  const bool nt = !g.odd && pop_bytes > kCacheBytes;
+  const bool nt = read_streams(static_cast<uint64_t>(g.nx) * storage_bytes(storage), pop_bytes, g.odd != 0);
   return with_storage(storage, [&](auto st) {
     constexpr int S = decltype(st)::value;
     const auto kernel = g.odd ? moments_kernel<S, true, false>

@@ -45,3 +45,13 @@ def test_largest_prime(evaluate):
     def prime(n):
         return max(d for d in range(2, n + 1) if n % d == 0 and all(d % k for k in range(2, d)))
     assert evaluate([f"largest_prime({n})" for n in range(2, 200)]) == [prime(n) for n in range(2, 200)]
+
+
+def test_reads_past_the_caches(evaluate):
+    """Even step counts, beyond 256 MiB, rows of whole 128-byte lines."""
+    def q(dims, size, odd=0):
+        return f"read_streams({dims[0] * size}, {27 * dims[0] * dims[1] * dims[2] * size}ull, {odd})"
+    yes = [((192, 192, 192), 4), ((256, 256, 256), 2), ((96, 256, 256), 4), ((288, 256, 256), 4)]
+    no = [((128, 128, 128), 4), ((255, 256, 200), 2), ((255, 256, 200), 4), ((288, 256, 256), 2), ((200, 200, 200), 4),
+          ((1000, 64, 100), 4), ((16, 512, 512), 4), ((8, 1024, 600), 4), ((192, 192, 192), 4, 1)]
+    assert evaluate([q(*c) for c in yes + no]) == [1] * len(yes) + [0] * len(no)
