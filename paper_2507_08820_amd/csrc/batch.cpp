@@ -16,6 +16,7 @@
 #include <cstring>
 #include <fstream>
 #include <new>
+#include <numeric>
 #include <sstream>
 #include <string>
 #include <vector>
@@ -23,6 +24,7 @@
 #include "../../include/rflbm.h"
 #include "kernels.hpp"
 #include "lattice.hpp"
+#include "policy.hpp"
 #include "storage.hpp"
 
 using namespace rflbm;
@@ -84,6 +86,8 @@ struct rflbm_batch {
   std::vector<rflbm_params> p;
   BatchLayout B;
   uint64_t pop_bytes = 0;  // populations of all replicas
+  uint64_t row_gcd = 0;    // greatest common divisor of their population rows, bytes
+  uint64_t largest_nodes = 0;
   uint8_t* buf = nullptr;
   bool owns_buf = false;
   hipStream_t stream = nullptr;
@@ -151,15 +155,12 @@ rflbm_status upload_tables(rflbm_batch* b) {
   return RFLBM_OK;
 }
 
-// Neighbouring tiles on one XCD meet in its L2: 8 boxes of 20^3 FP32 7.8 -> 5.6 us
-// a step, 24 of 8^3..32^3 FP16 15.0 -> 12.6, 32 of 96^3 FP32 1102 -> 1076, 64 of
-// 32^3..96^3 FP32 831 -> 825.  Large 16-bit batches, held by arithmetic, are
-// better off with the tiles dealt in turn (64 of 32^3..96^3 433 -> 441).
+// One range of tiles per XCD (else tiles dealt in turn).
 bool xcd_ranges(const rflbm_batch* b) {
-  return b->p[0].storage == RFLBM_F32 || b->pop_bytes <= kStreamBytes;
+  return batch_in_ranges(b->pop_bytes, b->row_gcd, b->p[0].storage == RFLBM_F32, b->bpc <= 0);
 }
 
-BatchArgs batch_args(const rflbm_batch* b, uint32_t step_offset) {
+BatchArgs batch_args(const rflbm_batch* b, uint32_t step_offset, bool stats) {
   BatchArgs a;
   a.reps = reinterpret_cast<const ReplicaArgs*>(b->buf + b->B.reps_off);
   a.tile_rep = reinterpret_cast<const uint32_t*>(b->buf + b->B.tiles_off);
@@ -168,7 +169,7 @@ BatchArgs batch_args(const rflbm_batch* b, uint32_t step_offset) {
   a.step_offset = step_offset;
   a.partial_pitch = b->B.max_tiles;
   a.partials = reinterpret_cast<double*>(b->buf + b->B.partials_off);
-  a.pop_bytes = b->pop_bytes;
+  a.even_nt = batch_even_nt(b->pop_bytes, b->row_gcd, b->p[0].storage == RFLBM_F32, stats, b->largest_nodes) ? 1u : 0u;
   a.xcd_ranges = xcd_ranges(b) ? 1u : 0u;
   return a;
 }
@@ -186,8 +187,8 @@ uint32_t batch_grid(const rflbm_batch* b) {
 // Enqueues the step at time t, whose Philox step count is the device counter
 // plus `offset`, with its statistics when t is a sampled step.
 hipError_t enqueue_step(rflbm_batch* b, int64_t t, uint32_t offset, hipStream_t s) {
-  const BatchArgs a = batch_args(b, offset);
   const bool stats = stats_step(b, t);
+  const BatchArgs a = batch_args(b, offset, stats);
   hipError_t e = launch_batch_step(b->p[0].storage, (t & 1) != 0, b->rounds, b->all_ghost_eq, stats, a,
                                    batch_grid(b), b->tile, s);
   if (e == hipSuccess && stats) e = launch_batch_stats_reduce(a, static_cast<uint32_t>(b->n), b->tile, s);
@@ -355,6 +356,8 @@ rflbm_status rflbm_batch_create(int32_t n, const rflbm_params* p, void* dev_buf,
     lattice_init(v, p[r], b->buf + B.region_off[r], b->stream, false);  // plain layout
     v->is_view = true;
     b->pop_bytes += v->L.pop_bytes;
+    b->row_gcd = std::gcd(b->row_gcd, static_cast<uint64_t>(v->L.pop_pitch));
+    b->largest_nodes = std::max(b->largest_nodes, node_count(p[r]));
     b->views.push_back(v);
     if (lattice_clear(v) != hipSuccess) {
       rflbm_batch_destroy(b);

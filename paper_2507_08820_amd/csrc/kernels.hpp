@@ -109,7 +109,7 @@ struct BatchArgs {
   uint32_t step_offset;                  // t mod 2^32 = *step + step_offset
   uint32_t partial_pitch;                // doubles between partial columns (>= ntiles)
   double* partials;                      // statistics partials [kNumStats][partial_pitch]
-  uint64_t pop_bytes;                    // populations of all replicas
+  uint32_t even_nt;                      // 1: non-temporal population accesses on even steps
   uint32_t xcd_ranges;                   // 1: one range of tiles per XCD (the grid a multiple of 8)
 };
 

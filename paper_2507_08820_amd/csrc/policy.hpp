@@ -20,6 +20,43 @@ inline bool read_streams(uint64_t row_bytes, uint64_t pop_bytes, bool odd) {
   return !odd && pop_bytes > kCacheBytes && row_bytes % kLineBytes == 0;
 }
 
+// Batches.  pop_bytes: populations of all replicas; rows: the greatest common
+// divisor of their population-row lengths in bytes.
+//
+// Streaming batches are larger than what the memory-side cache keeps from step to
+// step.  Whole-line rows lose the cache at its size (3 x 96^3 FP32, 273 MiB: 113 us a
+// step, streamed 97; 90 of 32^3, 304 MiB: 105, 103), others a little beyond it
+// (26 x 48^3, 296 MiB: 122, streamed 126; 60 x 48^3, 683 MiB: 324, 300).
+inline bool batch_streams(uint64_t pop_bytes, uint64_t rows) {
+  return pop_bytes > (rows % kLineBytes == 0 ? kCacheBytes : 320ull << 20);
+}
+
+// Non-temporal accesses of an even step of a streaming batch.  They fetch or write
+// a line once for every population row that shares it, which pays in FP32 with at
+// least half lines and in 16 bits with whole ones (us a step, non-temporal /
+// default: 64 of 32^3..96^3 FP32 959 / 1013, 60 x 48^3 FP32 300 / 324, 4 x 128^3
+// FP16 187 / 195; but 12 x 100^3 FP32 793 / 618, 20 of 130 x 50 x 70 FP32 596 / 458,
+// 64 of 32^3..96^3 FP16 568 / 551, 32 x 96^3 FP16 781 / 748).  A sampled step also
+// leaves its partials in the caches for the kernel that adds them: whole sectors are
+// enough (64 of 32^3..96^3 FP16 with statistics every other step 602 / 621, 16 of
+// them 236 / 246; 12 x 100^3 FP16 528 / 473), or replicas so large that this kernel,
+// a block a replica, weighs more than the step (200^3 FP16 859 / 947, 180^3 606 / 695).
+inline bool batch_even_nt(uint64_t pop_bytes, uint64_t rows, bool f32, bool stats, uint64_t largest_nodes) {
+  if (stats && largest_nodes > 1u << 22 && pop_bytes > kCacheBytes) return true;
+  if (!batch_streams(pop_bytes, rows)) return false;
+  return rows % (f32 ? kLineBytes / 2 : kLineBytes) == 0 || (stats && rows % 32 == 0);
+}
+
+// One range of tiles per XCD instead of tiles dealt in turn: neighbouring tiles then
+// meet in its L2, 8 x 20^3 FP32 7.6 -> 5.5 us a step, 24 of 8^3..32^3 FP16 7.4 -> 6.5,
+// 8 x 64^3 FP32 69 -> 67.  Streaming batches lose by it (4 x 128^3 FP32 340 -> 350, 64 of
+// 32^3..96^3 FP32 959 -> 989, 40 x 64^3 FP16 232 -> 237, 12 x 100^3 FP32 618 -> 647), but for
+// FP32 beyond 2 GiB at one block a tile (64 of 32^3..96^3 835 -> 829, 32 x 96^3 1098
+// -> 1073; 30 of 32^3..96^3, 1.3 GiB, 475 -> 487).
+inline bool batch_in_ranges(uint64_t pop_bytes, uint64_t rows, bool f32, bool block_a_tile) {
+  return !batch_streams(pop_bytes, rows) || (f32 && block_a_tile && pop_bytes > 2ull << 30);
+}
+
 // Largest prime factor of n >= 2.
 inline uint32_t largest_prime(uint32_t n) {
   uint32_t p = 1;

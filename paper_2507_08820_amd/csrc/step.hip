@@ -411,10 +411,7 @@ __global__ void __launch_bounds__(kMaxRowWaves * 64) step_row_kernel(const StepA
 // parity is a template parameter, and the host only replays graphs of an even
 // number of steps from an even step count.  kGhostsEq: every replica has every
 // omega_g = 1; otherwise each replica's own setting is read at run time.
-// NT: even steps of FP32 batches beyond the memory-side cache (64 replicas of
-// 32^3..96^3, 2.3 GB: 826 us a step, 905 without); the rows of 16-bit replicas
-// are too short for whole lines (451 with, 438 without), and small batches stay
-// in the cache (24 of 8^3..32^3, FP32: 17.0 with, 13.4 without).
+// NT: non-temporal accesses on even steps (batch_even_nt, policy.hpp).
 // STATS: each tile's statistics are reduced in the block (fixed order, FP64)
 // into column t of b.partials, for batch_stats_reduce.
 template <int S, bool ODD, int ROUNDS, int GHOSTS, bool STATS, bool NT>
@@ -796,7 +793,7 @@ hipError_t launch_batch_step(int storage, bool odd, int rounds, bool all_ghost_e
   if (tile != 128 && tile != 256) return hipErrorInvalidConfiguration;
   if (stats && !b.partials) return hipErrorInvalidValue;
   const dim3 g(grid), blk(tile);
-  const bool nt = storage == kF32 && !odd && b.pop_bytes > kStreamBytes;
+  const bool nt = !odd && b.even_nt != 0;
 #define RFLBM_BATCH_NT(S, O, R, G, N)                                                          \
   if (stats)                                                                                   \
     hipLaunchKernelGGL((batch_kernel<S, O, R, G, true, N>), g, blk, 0, stream, b);             \
@@ -804,7 +801,7 @@ hipError_t launch_batch_step(int storage, bool odd, int rounds, bool all_ghost_e
     hipLaunchKernelGGL((batch_kernel<S, O, R, G, false, N>), g, blk, 0, stream, b);
 #define RFLBM_BATCH_ST(S, O, R, G)                                                             \
   if (nt) {                                                                                    \
-    RFLBM_BATCH_NT(S, O, R, G, (S == kF32 && !O))                                              \
+    RFLBM_BATCH_NT(S, O, R, G, !O)                                              \
   } else {                                                                                     \
     RFLBM_BATCH_NT(S, O, R, G, false)                                                          \
   }

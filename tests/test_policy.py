@@ -55,3 +55,26 @@ def test_reads_past_the_caches(evaluate):
     no = [((128, 128, 128), 4), ((255, 256, 200), 2), ((255, 256, 200), 4), ((288, 256, 256), 2), ((200, 200, 200), 4),
           ((1000, 64, 100), 4), ((16, 512, 512), 4), ((8, 1024, 600), 4), ((192, 192, 192), 4, 1)]
     assert evaluate([q(*c) for c in yes + no]) == [1] * len(yes) + [0] * len(no)
+
+
+MIB = 1 << 20
+
+
+def test_batches(evaluate):
+    """(populations, row lengths in bytes, FP32, sampled step, largest replica):
+    default or non-temporal even steps, ranges or turns, as measured."""
+    cases = [  # MiB, gcd of the rows, f32, stats, nodes of the largest, blocks a tile -> nt, ranges
+        ((7, 80, 1, 0, 20 ** 3, 0), (0, 1)), ((216, 256, 1, 0, 64 ** 3, 0), (0, 1)), ((216, 256, 0, 0, 128 ** 3, 0), (0, 1)),
+        ((273, 384, 1, 0, 96 ** 3, 0), (1, 0)), ((273, 384, 1, 1, 96 ** 3, 0), (1, 0)), ((304, 128, 1, 0, 32 ** 3, 0), (1, 0)),
+        ((296, 192, 1, 0, 48 ** 3, 0), (0, 1)), ((683, 192, 1, 0, 48 ** 3, 0), (1, 0)), ((309, 400, 1, 0, 10 ** 6, 0), (0, 1)),
+        ((1236, 400, 1, 0, 10 ** 6, 0), (0, 0)), ((937, 520, 1, 1, 455000, 0), (0, 0)), ((864, 512, 1, 0, 128 ** 3, 0), (1, 0)),
+        ((864, 512, 1, 0, 128 ** 3, 1), (1, 0)), ((2223, 64, 1, 0, 96 ** 3, 0), (1, 0)), ((2223, 64, 1, 0, 96 ** 3, 1), (1, 1)),
+        ((1304, 64, 1, 0, 96 ** 3, 1), (1, 0)), ((432, 256, 0, 0, 128 ** 3, 0), (1, 0)), ((432, 256, 0, 1, 128 ** 3, 1), (1, 0)),
+        ((540, 128, 0, 0, 64 ** 3, 0), (1, 0)), ((1111, 32, 0, 0, 96 ** 3, 0), (0, 0)), ((1111, 32, 0, 1, 96 ** 3, 0), (1, 0)),
+        ((1458, 192, 0, 0, 96 ** 3, 1), (0, 0)), ((618, 200, 0, 0, 10 ** 6, 0), (0, 0)), ((618, 200, 0, 1, 10 ** 6, 0), (0, 0)),
+        ((824, 400, 0, 1, 200 ** 3, 0), (1, 0)), ((300, 360, 0, 1, 180 ** 3, 0), (1, 1)), ((141, 260, 0, 0, 455000, 0), (0, 1)),
+    ]
+    got = evaluate([e for (mb, rows, f32, stats, n, tile), _ in cases for e in (
+        f"batch_even_nt({mb * MIB}ull, {rows}, {f32}, {stats}, {n})",
+        f"batch_in_ranges({mb * MIB}ull, {rows}, {f32}, {tile})")])
+    assert [c for c, a, b in zip(cases, got[::2], got[1::2]) if (a, b) != c[1]] == []
