@@ -17,6 +17,7 @@
 #include "d3q27.hpp"
 #include "kernels.hpp"
 #include "lattice.hpp"
+#include "policy.hpp"
 #include "sk.hpp"
 #include "storage.hpp"
 
@@ -187,6 +188,18 @@ GatherArgs gather_args(const rflbm_lattice* L, const rflbm_params& p, int64_t t)
 
 namespace rflbm {
 
+// The lattice as the rules of policy.hpp see it.
+static StepBox step_box(const rflbm_lattice* L) {
+  StepBox b;
+  b.nx = static_cast<uint32_t>(L->p.nx);
+  b.value_bytes = storage_bytes(L->p.storage);
+  b.noise = L->p.kT > 0.0;
+  b.row_blocks = L->row_mode;
+  b.in_4gib = static_cast<uint64_t>(L->p.nz >> L->L.bz_log) * L->L.plane_pitch < (1ull << 32);
+  b.turn_bytes = L->turn_bytes;
+  return b;
+}
+
 StepArgs step_args(const rflbm_lattice* L) {
   const rflbm_params& p = L->p;
   StepArgs a;
@@ -202,7 +215,7 @@ StepArgs step_args(const rflbm_lattice* L) {
   a.by_log = L->L.by_log;
   a.bz_log = L->L.bz_log;
   a.plane_pitch = L->L.plane_pitch;
-  a.turn_bytes = L->turn_bytes;
+  a.streams = step_streams(step_box(L)) ? 1u : 0u;
   a.tiles_x = (p.nx + L->launch.bx - 1) / L->launch.bx;
   a.tiles_y = (p.ny + L->launch.by - 1) / L->launch.by;
   a.ntiles = a.tiles_x * a.tiles_y * static_cast<uint32_t>(p.nz);
@@ -262,30 +275,6 @@ void lattice_init(rflbm_lattice* L, const rflbm_params& p, uint8_t* buf, hipStre
   L->launch = make_launch(p.nx, p.ny, p.nz, p.nx >= 256 ? 256 : (p.nx >= 128 ? 128 : 64),
                           p.nx >= 256 ? 1 : (p.nx >= 128 ? 2 : 4));
   L->row_mode = true;
-}
-
-// Row-aligned blocks pay off where the step is bandwidth bound: FP32 storage,
-// or no noise (16-bit at 512^3 without noise: 2.46 ms per step against 2.74 ms
-// tiled).  The 16-bit steps with noise are bound by arithmetic: there the lane
-// moves and barriers of the whole-row odd step cost more than the aligned
-// accesses save (3.8 against 3.2 ms).
-static bool rows_pay(const rflbm_lattice* L) {
-  return L->row_mode && (L->p.storage == RFLBM_F32 || L->p.kT == 0.0);
-}
-
-static bool odd_in_rows(const rflbm_lattice* L) { return rows_pay(L) && row_kernel_fits(L->p.nx); }
-
-// Steps without statistics in one-wave blocks (nx a multiple of 64): the even
-// ones of the lattices above, and the odd ones too long for a block; the 16-bit
-// steps with noise of both parities, whose rows then fill every wave (us per
-// step against the tiles of 128 or 256 nodes: 192^3 FP16 140 / 177, 320 x 96 x
-// 96 FP16 55 / 83, 192 x 128 x 128 BF16 57 / 75, 128^3 FP16 40.4 / 43.8), except
-// where tiles of 256 fit the rows and the box streams from memory (256^3 341 /
-// 336, 512^3 2773 / 2713).
-static bool in_waves(const rflbm_lattice* L, const StepArgs& a, bool odd) {
-  if (!L->row_mode || L->p.nx % 64 != 0) return false;
-  if (rows_pay(L)) return !odd || !row_kernel_fits(L->p.nx);
-  return !(L->p.nx % 256 == 0 && streams(a));
 }
 
 hipError_t lattice_clear(rflbm_lattice* L) {
@@ -371,6 +360,7 @@ rflbm_status lattice_set_params(rflbm_lattice* L, const rflbm_params* p) {
 rflbm_status lattice_steps(rflbm_lattice* L, int64_t nsteps) {
   if (nsteps < 0) return fail(RFLBM_EINVAL, "nsteps must be >= 0");
   StepArgs a = step_args(L);
+  const StepBox box = step_box(L);
   const int rounds = L->p.kT > 0.0 ? static_cast<int>(L->p.philox_rounds) : 0;
   double* acc = reinterpret_cast<double*>(L->buf + L->L.acc_off);
   double* scratch = reinterpret_cast<double*>(L->buf + L->L.scratch_off);
@@ -391,18 +381,20 @@ rflbm_status lattice_steps(rflbm_lattice* L, int64_t nsteps) {
     a.partials = partials + waiting * slot_pitch;
     uint32_t grid = L->launch.grid;  // blocks, hence statistics partials, of the kernel used
     hipError_t e;
-    if (L->row_mode && flat_kernel_fits(a)) {
-      e = launch_step_flat(L->p.storage, odd, rounds, stats, a, L->stream);
-      grid = flat_grid(a, stats);
-    } else if ((odd || stats) && odd_in_rows(L)) {
-      // whole rows: odd steps, and even steps with statistics (one partial per
-      // row; the one-wave even blocks would write one per wave)
-      e = launch_step_row(L->p.storage, odd, rounds, stats, a, L->stream);
-      grid = row_grid(L->p.ny, L->p.nz);
-    } else if (!stats && in_waves(L, a, odd)) {
-      e = launch_step_wave(L->p.storage, odd, rounds, a, L->stream);
-    } else {
-      e = launch_step(L->p.storage, odd, rounds, stats, a, L->launch, L->stream);
+    switch (step_route(box, odd, stats)) {
+      case StepRoute::kFlat:
+        e = launch_step_flat(L->p.storage, odd, rounds, stats, a, L->stream);
+        grid = flat_grid(a, stats);
+        break;
+      case StepRoute::kRows:
+        e = launch_step_row(L->p.storage, odd, rounds, stats, a, L->stream);
+        grid = row_grid(L->p.ny, L->p.nz);
+        break;
+      case StepRoute::kWaves:
+        e = launch_step_wave(L->p.storage, odd, rounds, a, L->stream);
+        break;
+      default:
+        e = launch_step(L->p.storage, odd, rounds, stats, a, L->launch, L->stream);
     }
     if (e != hipSuccess) {
       (void)fold();  // the steps before it count
@@ -806,7 +798,7 @@ rflbm_status rflbm_set_row_blocks(rflbm_lattice* L, int32_t enable) {
 rflbm_status rflbm_get_row_blocks(const rflbm_lattice* L, int32_t* active) {
   if (rflbm_status s = check_lattice(L)) return s;
   if (!active) return fail(RFLBM_EINVAL, "active is NULL");
-  *active = odd_in_rows(L) ? 1 : 0;
+  *active = step_route(step_box(L), true, false) == StepRoute::kRows ? 1 : 0;
   return RFLBM_OK;
 }
 

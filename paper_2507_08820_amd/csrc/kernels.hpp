@@ -44,7 +44,7 @@ struct StepArgs {
   uint32_t zin_pitch;    // bytes from one x-row block to the next in z inside a brick (Zi)
   uint32_t by_log, bz_log;  // log2 of the brick shape By x Bz (0, 0: plain layout)
   uint64_t plane_pitch;  // bytes from one brick row (Bz z planes) to the next (P)
-  uint64_t turn_bytes;   // populations stepped in turn with these, and these (cache policy)
+  uint32_t streams;      // 1: non-temporal population accesses (step_streams, policy.hpp)
   uint32_t tiles_x;      // tiles along x (tile = blockDim.x x blockDim.y nodes of one z plane)
   uint32_t tiles_y;      // tiles along y
   uint32_t ntiles;       // tiles_x * tiles_y * nz
@@ -113,10 +113,6 @@ struct BatchArgs {
   uint32_t xcd_ranges;                   // 1: one range of tiles per XCD (the grid a multiple of 8)
 };
 
-// Populations beyond which a box or batch streams from memory: larger than what
-// the memory-side cache keeps from one step to the next (step.hip).
-constexpr uint64_t kStreamBytes = 320ull << 20;
-
 // One step of every replica (persistent grid of `grid` blocks walking the tiles);
 // the Philox step count is *b.step + b.step_offset, and the parity `odd` must
 // match it.  all_ghost_eq: every replica has every omega_g = 1 (then the
@@ -157,10 +153,6 @@ uint32_t row_grid(uint32_t ny, uint32_t nz);
 
 // Bytes from the first to past the last population row of the box.
 uint64_t pop_span(const StepArgs& a);
-// True when the box, or the batch whose replicas are stepped one by one, is too
-// large for the memory-side cache to hold what a step writes until the next step
-// reads it.
-bool streams(const StepArgs& a);
 // True when a step can run in flat blocks: rows that do not fill whole waves, in
 // a box whose populations lie within 4 GiB.
 bool flat_kernel_fits(const StepArgs& a);

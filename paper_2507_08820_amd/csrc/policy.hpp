@@ -20,6 +20,76 @@ inline bool read_streams(uint64_t row_bytes, uint64_t pop_bytes, bool odd) {
   return !odd && pop_bytes > kCacheBytes && row_bytes % kLineBytes == 0;
 }
 
+// One box as the choice of its step kernel sees it.
+struct StepBox {
+  uint32_t nx;
+  uint32_t value_bytes;  // of a stored population
+  bool noise;
+  bool row_blocks;       // blocks that follow the rows, not tiles alone
+  bool in_4gib;          // populations within 4 GiB
+  uint64_t turn_bytes;   // populations stepped in turn with these, and these
+};
+
+// kTiles: step_kernel, kFlat: step_flat_kernel, kRows: step_row_kernel, kWaves: step_wave_kernel.
+enum class StepRoute { kTiles, kFlat, kRows, kWaves };
+
+// Memory, not arithmetic, holds these steps: FP32, and 16 bits without noise.
+inline bool memory_bound(const StepBox& b) { return b.value_bytes == 4 || !b.noise; }
+
+// Non-temporal accesses of the steps that have them: even ones in waves, both
+// parities in rows, even ones in flat blocks.
+//
+// Rows of whole waves, beyond 320 MiB (us a step with / without, FP32: 216 MiB
+// (128^3) 81 / 65, 270 MiB 103 / 84, 338 MiB 126 / 123, 506 MiB 184 / 197, 1.7 GiB
+// (256^3) 599 / 653; FP16 without noise 324 MiB 134 / 137, 864 MiB 303 / 328).
+// Flat blocks: FP32 rows of whole or half lines beyond 256 MiB (160 x 160 x 100, 264 MiB,
+// 85 / 95, 96 x 256 x 256 235 / 265, 416 x 200 x 200 647 / 688, 16 x 700 x 700 321 / 338);
+// other rows share their lines with neighbours (300 x 200 x 100 318 / 255, 96^2 x
+// 300 FP16 201 / 196).
+inline bool step_streams(const StepBox& b) {
+  if (b.nx % 64 != 0) return b.value_bytes == 4 && b.nx % 16 == 0 && b.turn_bytes > kCacheBytes;
+  return b.turn_bytes > 320ull << 20;
+}
+
+// The kernel of one step.
+//
+// Rows that do not fill waves, within 4 GiB: flat blocks, which leave no lane idle
+// (figures at step_flat_kernel).  Beyond 256 MiB, where the odd step streams from memory,
+// tiles keep what they lose few lanes on: rows of 33 to 63 nodes (FP32 63 x 300 x
+// 140 flat 114, tiles 98, 56 x 200 x 300 141 / 124, 48 x 300 x 300 187 / 161; from 45 in 16
+// bits, 63 x 300 x 280 FP16 143 / 118, 58 x 400 x 400 245 / 208, but 40 x 400 x 400 164 / 171),
+// and FP32 rows of whole or half lines that fill 15 of 16 lanes of their tiles of 256
+// (736 x 100 x 96 265 streamed, tiles 258, 2016 x 48 x 48 172 / 167, 1008 x 80 x 80 261 /
+// 251; but 464 x 120 x 120 275 / 274, 352 x 256 x 128 439 / 456).
+//
+// Rows of whole waves: memory-bound steps in whole rows up to 1024 nodes (odd ones,
+// and even ones with statistics: one partial a row, not one a wave), else in waves.
+// 16 bits with noise, bound by arithmetic, in waves of both parities: there the
+// lane moves and barriers of the whole-row odd step cost more than aligned accesses
+// save (512^3 3.8 / 3.2 ms), and waves leave no lane idle (us a step in waves / tiles of
+// 128 or 256: 192^3 FP16 140 / 177, 320 x 96 x 96 FP16 55 / 83, 192 x 128 x 128 BF16
+// 57 / 75, 128^3 FP16 40.4 / 43.8), except where tiles of 256 fit the rows and the box
+// streams from memory (256^3 341 / 336, 512^3 2773 / 2713).
+inline StepRoute step_route(const StepBox& b, bool odd, bool stats) {
+  if (!b.row_blocks) return StepRoute::kTiles;
+  const bool f32 = b.value_bytes == 4;
+  if (b.nx % 64 != 0) {
+    if (!b.in_4gib) return StepRoute::kTiles;
+    if (b.turn_bytes > kCacheBytes) {
+      if (b.nx >= (f32 ? 33u : 45u) && b.nx <= 63) return StepRoute::kTiles;
+      const uint32_t lanes = (b.nx + 255) / 256 * 256;
+      if (f32 && b.nx % 16 == 0 && b.nx >= 256 && 16 * b.nx >= 15 * lanes) return StepRoute::kTiles;
+    }
+    return StepRoute::kFlat;
+  }
+  if (memory_bound(b)) {
+    if ((odd || stats) && b.nx <= 1024) return StepRoute::kRows;
+    return stats ? StepRoute::kTiles : StepRoute::kWaves;
+  }
+  if (stats || (b.nx % 256 == 0 && step_streams(b))) return StepRoute::kTiles;
+  return StepRoute::kWaves;
+}
+
 // Batches.  pop_bytes: populations of all replicas; rows: the greatest common
 // divisor of their population-row lengths in bytes.
 //

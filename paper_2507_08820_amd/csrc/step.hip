@@ -61,20 +61,15 @@ constexpr int kStatPitch = kBlock + kBlock / 32;
 __device__ __forceinline__ constexpr uint32_t stat_at(uint32_t tid) { return tid + (tid >> 5); }
 
 
-// Cache policy of the population accesses (NT in the kernels' scope: non-temporal).
-// Even steps, and odd steps in whole rows, read and write whole cache lines
-// that no other wave touches and that the step uses once; odd steps in other
-// blocks share the lines at the ends of their +-1-shifted ranges with
-// neighbouring waves and always keep the default policy, so that those meet in
-// L2.  Rows that are not aligned to lines keep it at both parities: with
-// non-temporal even steps 200^3 FP16 takes 244 us a step instead of 199, 300 x
-// 280 x 260 BF16 684 instead of 533.
-//
-// NT pays where the populations exceed what the 256 MiB memory-side cache still
-// holds of them from the last step: us per step with / without NT, FP32,
-// 216 MiB (128^3) 81 / 65, 270 MiB 103 / 84, 338 MiB 126 / 123, 506 MiB
-// 184 / 197, 1.7 GiB (256^3) 599 / 653; BF16 without noise 108 MiB (128^3)
-// 41 / 29, 324 MiB 134 / 137 (FP16), 864 MiB 303 / 328 (kStreamBytes).
+// Cache policy of the population accesses (NT in the kernels' scope: non-temporal;
+// where it pays: step_streams and batch_even_nt, policy.hpp).  Even steps, and odd
+// steps in whole rows, read and write whole cache lines that no other wave touches
+// and that the step uses once; odd steps in other blocks share the lines at the
+// ends of their +-1-shifted ranges with neighbouring waves and always keep the
+// default policy, so that those meet in L2.  Even tiles, the only kernel without
+// the choice, are always non-temporal: they run beyond the cache, on sampled steps
+// of 16-bit boxes with noise (192^3 FP16, every step sampled: 198 us, default policy 208;
+// 128^3 55.5, 52.5), and where row blocks are off.
 
 // Visiting order of the whole-row odd step: groups of 2 rows x 8 planes
 // (measured at 512^3: about 1 % faster than plain row order).
@@ -287,7 +282,7 @@ __global__ void __launch_bounds__(kBlock) step_kernel(const StepArgs a) {
 // 5.0; large boxes do not care, except with statistics, whose staging and
 // partials weigh more (us per step in blocks of 64 / 256: 16^3 5.3 / 6.1, 17 x 19
 // x 23 5.4 / 6.6, 48^3 FP16 11.8 / 8.1, 100^3 49 / 40; flat_block).
-template <int S, bool ODD, int ROUNDS, bool STATS, int GHOSTS, int BLOCK>
+template <int S, bool ODD, int ROUNDS, bool STATS, int GHOSTS, int BLOCK, bool NT>
 __global__ void __launch_bounds__(BLOCK) step_flat_kernel(const StepArgs a) {
   uint32_t tile = blockIdx.x;
   if (a.xcd_remap) tile = (tile & 7u) * (gridDim.x >> 3) + (tile >> 3);
@@ -307,7 +302,6 @@ __global__ void __launch_bounds__(BLOCK) step_flat_kernel(const StepArgs a) {
     constexpr bool BRICKS = true;
     constexpr bool ROW_SHIFT = false;
     constexpr bool GHOST_REC = GHOSTS == kGhostsRec, GHOST_EQ = GHOSTS == kGhostsEq;
-    constexpr bool NT = false;
     [[maybe_unused]] uint32_t (*row_edge_in)[kMaxRowWaves] = nullptr;
     [[maybe_unused]] uint32_t (*row_edge_out)[kMaxRowWaves] = nullptr;
 #include "node_body.inc"
@@ -608,8 +602,13 @@ uint32_t flat_block(const StepArgs& a, bool stats) {
 
 template <int S, bool ODD, int R, bool ST, int BLOCK>
 void launch_flat_b(const StepArgs& a, uint32_t grid, hipStream_t s) {
+  constexpr bool kHasNt = S == kF32 && !ODD;  // the steps that stream
   by_ghosts(a, [&](auto gh) {
-    hipLaunchKernelGGL((step_flat_kernel<S, ODD, R, ST, decltype(gh)::value, BLOCK>), dim3(grid), dim3(BLOCK), 0, s, a);
+    constexpr int G = decltype(gh)::value;
+    if (kHasNt && a.streams)
+      hipLaunchKernelGGL((step_flat_kernel<S, ODD, R, ST, G, BLOCK, kHasNt>), dim3(grid), dim3(BLOCK), 0, s, a);
+    else
+      hipLaunchKernelGGL((step_flat_kernel<S, ODD, R, ST, G, BLOCK, false>), dim3(grid), dim3(BLOCK), 0, s, a);
   });
 }
 
@@ -702,18 +701,16 @@ hipError_t launch_wave_s(int rounds, const StepArgs& a, uint32_t grid, hipStream
 template <int S>
 hipError_t launch_wave_p(bool odd, int rounds, const StepArgs& a, uint32_t grid, hipStream_t s) {
   if (odd) return launch_wave_s<S, true, false>(rounds, a, grid, s);  // odd steps keep the default policy
-  return streams(a) ? launch_wave_s<S, false, true>(rounds, a, grid, s) : launch_wave_s<S, false, false>(rounds, a, grid, s);
+  return a.streams ? launch_wave_s<S, false, true>(rounds, a, grid, s) : launch_wave_s<S, false, false>(rounds, a, grid, s);
 }
 
 template <int S>
 hipError_t launch_row_p(bool odd, bool stats, int rounds, const StepArgs& a, uint32_t grid, hipStream_t s) {
-  return streams(a) ? launch_row_st<S, true>(odd, stats, rounds, a, grid, s)
+  return a.streams ? launch_row_st<S, true>(odd, stats, rounds, a, grid, s)
                     : launch_row_st<S, false>(odd, stats, rounds, a, grid, s);
 }
 
 }  // namespace
-
-bool streams(const StepArgs& a) { return a.turn_bytes > kStreamBytes; }
 
 hipError_t launch_step_wave(int storage, bool odd, int rounds, const StepArgs& a, hipStream_t stream) {
   if (a.nx % 64 != 0 || a.nx == 0) return hipErrorInvalidConfiguration;

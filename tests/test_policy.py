@@ -78,3 +78,58 @@ def test_batches(evaluate):
         f"batch_even_nt({mb * MIB}ull, {rows}, {f32}, {stats}, {n})",
         f"batch_in_ranges({mb * MIB}ull, {rows}, {f32}, {tile})")])
     assert [c for c, a, b in zip(cases, got[::2], got[1::2]) if (a, b) != c[1]] == []
+
+
+TILES, FLAT, ROWS, WAVES = range(4)
+BYTES = {"f32": 4, "f16": 2}
+
+
+def box(dims, storage, noise, row_blocks=1, in_turn=0):
+    """StepBox of a box by itself (or of `in_turn` MiB stepped in turn)."""
+    size = 27 * dims[0] * dims[1] * dims[2] * BYTES[storage]
+    return (f"StepBox{{{dims[0]}u, {BYTES[storage]}u, {str(bool(noise)).lower()}, {str(bool(row_blocks)).lower()}, "
+            f"{str(size < 1 << 32).lower()}, {in_turn * MIB if in_turn else size}ull}}")
+
+
+def routes(evaluate, cases):
+    """Cases (dims, storage, noise, odd, stats) whose route is not the one given."""
+    got = evaluate([f"step_route({box(d, s, n)}, {odd}, {st})" for (d, s, n, odd, st), _ in cases])
+    return [(c, g) for c, g in zip(cases, got) if g != c[1]]
+
+
+def test_rows_that_do_not_fill_waves(evaluate):
+    cases = []
+    for odd in (0, 1):
+        for stats in (0, 1):
+            flat = [((130, 50, 70), "f32"), ((17, 19, 23), "f32"), ((63, 128, 128), "f32"), ((48, 200, 220), "f32"),
+                    ((96, 256, 256), "f32"), ((32, 512, 512), "f32"), ((30, 500, 500), "f32"), ((464, 120, 120), "f32"),
+                    ((352, 256, 128), "f32"), ((1000, 80, 80), "f32"), ((255, 256, 200), "f32"), ((1270, 64, 64), "f32"),
+                    ((40, 400, 400), "f16"), ((63, 300, 240), "f16"), ((1008, 110, 110), "f16"), ((2000, 80, 80), "f16")]
+            tiles = [((63, 300, 140), "f32"), ((33, 320, 320), "f32"), ((48, 300, 300), "f32"), ((480, 120, 120), "f32"),
+                     ((736, 100, 96), "f32"), ((2016, 48, 48), "f32"), ((1264, 64, 64), "f32"), ((56, 300, 340), "f16"),
+                     ((63, 300, 280), "f16"), ((350, 350, 350), "f32")]
+            cases += [((d, s, noise, odd, stats), FLAT) for d, s in flat for noise in (0, 1)]
+            cases += [((d, s, noise, odd, stats), TILES) for d, s in tiles for noise in (0, 1)]
+    assert routes(evaluate, cases) == []
+    assert evaluate([f"step_route({box((130, 50, 70), 'f32', 1, row_blocks=0)}, 0, 0)"]) == [TILES]
+
+
+def test_streamed_flat_blocks(evaluate):
+    yes = [((96, 256, 256), "f32"), ((160, 160, 100), "f32"), ((416, 200, 200), "f32"), ((16, 700, 700), "f32"),
+           ((464, 120, 120), "f32"), ((1040, 80, 80), "f32")]
+    no = [((96, 200, 110), "f32"), ((300, 200, 100), "f32"), ((255, 256, 200), "f32"), ((40, 400, 400), "f32"),
+          ((96, 256, 256), "f16"), ((300, 280, 260), "f16")]
+    assert evaluate([f"step_streams({box(d, s, 1)})" for d, s in yes + no]) == [1] * len(yes) + [0] * len(no)
+
+
+def test_rows_of_whole_waves(evaluate):
+    cases = []
+    for d in [(64, 64, 64), (256, 256, 256), (1024, 64, 64), (320, 96, 96)]:
+        for s, noise in (("f32", 1), ("f32", 0), ("f16", 0)):
+            cases += [((d, s, noise, 0, 0), WAVES), ((d, s, noise, 1, 0), ROWS), ((d, s, noise, 0, 1), ROWS),
+                      ((d, s, noise, 1, 1), ROWS)]
+    for odd in (0, 1):
+        cases += [(((192, 192, 192), "f16", 1, odd, 0), WAVES), (((320, 96, 96), "f16", 1, odd, 0), WAVES),
+                  (((256, 128, 128), "f16", 1, odd, 0), WAVES), (((256, 256, 256), "f16", 1, odd, 0), TILES),
+                  (((192, 192, 192), "f16", 1, odd, 1), TILES)]
+    assert routes(evaluate, cases) == []
