@@ -253,7 +253,7 @@ __global__ void __launch_bounds__(kBlock) step_kernel(const StepArgs a) {
 
   if (active) {
     const uint32_t step = a.step;
-    constexpr bool STATS_WAVE = false;
+    constexpr bool STATS_WAVE = false, NOISE_FIRST = true;
     [[maybe_unused]] float (*stat_wave)[kMaxRowWaves] = nullptr;
     constexpr bool SMALL_BOX = false;
     constexpr bool BUFFER_ACCESS = true;
@@ -295,7 +295,7 @@ __global__ void __launch_bounds__(BLOCK) step_flat_kernel(const StepArgs a) {
     uint32_t y, z;
     brick_row(row, a, y, z);
     const uint32_t step = a.step;
-    constexpr bool STATS_WAVE = false;
+    constexpr bool STATS_WAVE = false, NOISE_FIRST = true;
     [[maybe_unused]] float (*stat_wave)[kMaxRowWaves] = nullptr;
     constexpr bool SMALL_BOX = true;
     constexpr bool BUFFER_ACCESS = true;
@@ -317,7 +317,7 @@ __global__ void __launch_bounds__(BLOCK) step_flat_kernel(const StepArgs a) {
 // order (brick_row; nx a multiple of 64).
 template <int S, int ROUNDS, int GHOSTS, bool ODD, bool NT>
 __global__ void __launch_bounds__(64) step_wave_kernel(const StepArgs a) {
-  constexpr bool STATS = false, SMALL_BOX = false, ROW_SHIFT = false, BUFFER_ACCESS = true;
+  constexpr bool STATS = false, SMALL_BOX = false, ROW_SHIFT = false, BUFFER_ACCESS = true, NOISE_FIRST = true;
   constexpr bool BRICKS = true;
   constexpr bool GHOST_REC = GHOSTS == kGhostsRec, GHOST_EQ = GHOSTS == kGhostsEq, STATS_WAVE = false;
   [[maybe_unused]] float (*stat_lds)[kStatPitch] = nullptr;
@@ -347,7 +347,7 @@ __global__ void __launch_bounds__(64) step_wave_kernel(const StepArgs a) {
 // kernel only for statistics (one partial per row instead of one per wave).
 template <int S, int ROUNDS, int GHOSTS, bool STATS, bool ODD, bool NT>
 __global__ void __launch_bounds__(kMaxRowWaves * 64) step_row_kernel(const StepArgs a) {
-  constexpr bool SMALL_BOX = false, ROW_SHIFT = ODD, BUFFER_ACCESS = true, BRICKS = true;
+  constexpr bool SMALL_BOX = false, ROW_SHIFT = ODD, BUFFER_ACCESS = true, BRICKS = true, NOISE_FIRST = true;
   constexpr bool GHOST_REC = GHOSTS == kGhostsRec, GHOST_EQ = GHOSTS == kGhostsEq, STATS_WAVE = true;
   [[maybe_unused]] float (*stat_lds)[kStatPitch] = nullptr;
   [[maybe_unused]] const uint32_t tid = 0;
@@ -414,6 +414,7 @@ __global__ void __launch_bounds__(kBlock) batch_kernel(const BatchArgs b) {
   [[maybe_unused]] float (*stat_wave)[kMaxRowWaves] = nullptr;
   constexpr bool SMALL_BOX = true;  // every replica region is below 4 GiB
   constexpr bool BRICKS = false;    // replicas keep the plain layout
+  constexpr bool NOISE_FIRST = false;
   // buffer instructions measured faster for 16-bit storage, global ones for
   // FP32 (64 replicas of 32^3..96^3: 38.9 vs 36.6 and 24.6 vs 25.9 GLUPS)
   constexpr bool BUFFER_ACCESS = S != kF32;
