@@ -41,14 +41,16 @@ inline bool memory_bound(const StepBox& b) { return b.value_bytes == 4 || !b.noi
 //
 // Rows of whole waves, beyond 320 MiB (us a step with / without, FP32: 216 MiB
 // (128^3) 81 / 65, 270 MiB 103 / 84, 338 MiB 126 / 123, 506 MiB 184 / 197, 1.7 GiB
-// (256^3) 599 / 653; FP16 without noise 324 MiB 134 / 137, 864 MiB 303 / 328).
+// (256^3) 599 / 653; FP16 without noise 324 MiB 134 / 137, 864 MiB 303 / 328); beyond
+// 1024 nodes, where odd steps are not in whole rows, beyond 256 MiB (1280 x 64 x 32
+// FP32, 270 MiB, 86 / 96, 1920 x 64 x 22 90 / 98, 1280 x 64 x 64 FP16 without noise 90 / 103).
 // Flat blocks: FP32 rows of whole or half lines beyond 256 MiB (160 x 160 x 100, 264 MiB,
 // 85 / 95, 96 x 256 x 256 235 / 265, 416 x 200 x 200 647 / 688, 16 x 700 x 700 321 / 338);
 // other rows share their lines with neighbours (300 x 200 x 100 318 / 255, 96^2 x
 // 300 FP16 201 / 196).
 inline bool step_streams(const StepBox& b) {
   if (b.nx % 64 != 0) return b.value_bytes == 4 && b.nx % 16 == 0 && b.turn_bytes > kCacheBytes;
-  return b.turn_bytes > 320ull << 20;
+  return b.turn_bytes > (b.nx <= 1024 ? 320ull << 20 : kCacheBytes);
 }
 
 // The kernel of one step.
@@ -64,6 +66,11 @@ inline bool step_streams(const StepBox& b) {
 //
 // Rows of whole waves: memory-bound steps in whole rows up to 1024 nodes (odd ones,
 // and even ones with statistics: one partial a row, not one a wave), else in waves.
+// Odd steps of longer rows in tiles of 256 where these fit: FP32 rows of a multiple
+// of 128 (1280 x 64 x 64 191 / 202 us a step in waves, 1920 x 64 x 96 461 / 474, 1152 x 96
+// x 96 412 / 424; 1088 x 64 x 64 163 / 159), 16 bits of a multiple of 256 when they
+// stream (2048 x 64 x 64 FP16 158 / 160, 1792 x 48 x 64 98 / 101; in the cache 1088 x 64
+// x 64 57 / 55).
 // 16 bits with noise, bound by arithmetic, in waves of both parities: there the
 // lane moves and barriers of the whole-row odd step cost more than aligned accesses
 // save (512^3 3.8 / 3.2 ms), and waves leave no lane idle (us a step in waves / tiles of
@@ -84,7 +91,8 @@ inline StepRoute step_route(const StepBox& b, bool odd, bool stats) {
   }
   if (memory_bound(b)) {
     if ((odd || stats) && b.nx <= 1024) return StepRoute::kRows;
-    return stats ? StepRoute::kTiles : StepRoute::kWaves;
+    if (stats) return StepRoute::kTiles;
+    return odd && (f32 ? b.nx % 128 == 0 : b.nx % 256 == 0 && step_streams(b)) ? StepRoute::kTiles : StepRoute::kWaves;
   }
   if (stats || (b.nx % 256 == 0 && step_streams(b))) return StepRoute::kTiles;
   return StepRoute::kWaves;

@@ -50,3 +50,19 @@ def test_rows_that_do_not_fill_waves_beyond_the_cache(rf, storage, dims, kT):
     n = sa["nodes"] * sa["samples"]
     for k in ("sum_drho2", "sum_j2", "sum_u2", "sum_pi2"):
         assert np.all(np.abs(sa[k] - sb[k]) <= n * 2.0 ** -53 * np.abs(sa[k])), k
+
+
+# rows longer than a block: odd steps in tiles and in waves, streamed and not
+LONG = [("f32", (1152, 3, 5)), ("f32", (1088, 3, 4)), ("f32", (1280, 50, 52)), ("f32", (1216, 50, 52)),
+        ("f16", (1280, 72, 70)), ("f16", (1088, 72, 80)), ("bf16", (2048, 5, 3))]
+
+
+@pytest.mark.parametrize("kT", [1e-4, 0.0])
+@pytest.mark.parametrize("storage,dims", LONG)
+def test_rows_longer_than_a_block(rf, storage, dims, kT):
+    kw = dict(storage=storage, kT=kT, tau=0.7, seed=6)
+    if storage != "f32" and kT == 0.0:
+        kw["storage_scale"] = 0.01
+    a, _ = run(rf, dims, True, 5, **kw)
+    b, _ = run(rf, dims, False, 5, **kw)
+    assert bool((a == b).all())

@@ -133,3 +133,18 @@ def test_rows_of_whole_waves(evaluate):
                   (((256, 128, 128), "f16", 1, odd, 0), WAVES), (((256, 256, 256), "f16", 1, odd, 0), TILES),
                   (((192, 192, 192), "f16", 1, odd, 1), TILES)]
     assert routes(evaluate, cases) == []
+
+
+def test_rows_longer_than_a_block(evaluate):
+    """Odd steps in tiles or waves, even ones in waves, streamed beyond 256 MiB."""
+    tiles = [((1280, 64, 64), "f32"), ((1152, 96, 96), "f32"), ((1920, 64, 22), "f32"), ((2048, 16, 16), "f32"),
+             ((2048, 64, 64), "f16"), ((1280, 64, 64), "f16"), ((1792, 48, 64), "f16")]
+    waves = [((1088, 64, 64), "f32"), ((1216, 64, 64), "f32"), ((4160, 16, 64), "f32"), ((1088, 64, 64), "f16"),
+             ((2048, 32, 64), "f16"), ((1920, 64, 96), "f16")]
+    cases = [((d, s, 0, 1, 0), TILES) for d, s in tiles] + [((d, s, 0, 1, 0), WAVES) for d, s in waves]
+    cases += [((d, s, 0, 0, 0), WAVES) for d, s in tiles + waves] + [((d, s, 0, 0, 1), TILES) for d, s in tiles + waves]
+    assert routes(evaluate, cases) == []
+    yes = [((1280, 64, 32), "f32", 1), ((1280, 64, 64), "f16", 0), ((256, 128, 96), "f32", 1), ((2048, 64, 64), "f32", 0)]
+    no = [((1088, 64, 32), "f32", 1), ((1280, 64, 56), "f16", 0), ((256, 128, 88), "f32", 1), ((1024, 64, 46), "f32", 1),
+          ((256, 256, 92), "f16", 0)]
+    assert evaluate([f"step_streams({box(*c)})" for c in yes + no]) == [1] * len(yes) + [0] * len(no)
