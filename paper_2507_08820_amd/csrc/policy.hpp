@@ -43,14 +43,16 @@ inline bool memory_bound(const StepBox& b) { return b.value_bytes == 4 || !b.noi
 // (128^3) 81 / 65, 270 MiB 103 / 84, 338 MiB 126 / 123, 506 MiB 184 / 197, 1.7 GiB
 // (256^3) 599 / 653; FP16 without noise 324 MiB 134 / 137, 864 MiB 303 / 328); beyond
 // 1024 nodes, where odd steps are not in whole rows, beyond 256 MiB (1280 x 64 x 32
-// FP32, 270 MiB, 86 / 96, 1920 x 64 x 22 90 / 98, 1280 x 64 x 64 FP16 without noise 90 / 103).
+// FP32, 270 MiB, 86 / 96, 1920 x 64 x 22 90 / 98, 1280 x 64 x 64 FP16 without noise 90 / 103),
+// and so 16 bits with noise (256 x 256 x 80 FP16, 270 MiB, 104 / 111, 192 x 192 x 140
+// 102 / 110, 256 x 256 x 72, 243 MiB, 91 / 85).
 // Flat blocks: FP32 rows of whole or half lines beyond 256 MiB (160 x 160 x 100, 264 MiB,
 // 85 / 95, 96 x 256 x 256 235 / 265, 416 x 200 x 200 647 / 688, 16 x 700 x 700 321 / 338);
 // other rows share their lines with neighbours (300 x 200 x 100 318 / 255, 96^2 x
 // 300 FP16 201 / 196).
 inline bool step_streams(const StepBox& b) {
   if (b.nx % 64 != 0) return b.value_bytes == 4 && b.nx % 16 == 0 && b.turn_bytes > kCacheBytes;
-  return b.turn_bytes > (b.nx <= 1024 ? 320ull << 20 : kCacheBytes);
+  return b.turn_bytes > (memory_bound(b) && b.nx <= 1024 ? 320ull << 20 : kCacheBytes);
 }
 
 // The kernel of one step.

@@ -66,3 +66,11 @@ def test_rows_longer_than_a_block(rf, storage, dims, kT):
     a, _ = run(rf, dims, True, 5, **kw)
     b, _ = run(rf, dims, False, 5, **kw)
     assert bool((a == b).all())
+
+
+@pytest.mark.parametrize("storage,dims", [("f16", (256, 250, 80)), ("bf16", (192, 190, 142))])
+def test_16_bit_steps_with_noise_at_the_size_of_the_cache(rf, storage, dims):
+    kw = dict(storage=storage, kT=1e-4, tau=0.7, seed=7)
+    a, _ = run(rf, dims, True, 5, **kw)
+    b, _ = run(rf, dims, False, 5, **kw)
+    assert bool((a == b).all())

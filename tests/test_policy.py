@@ -148,3 +148,12 @@ def test_rows_longer_than_a_block(evaluate):
     no = [((1088, 64, 32), "f32", 1), ((1280, 64, 56), "f16", 0), ((256, 128, 88), "f32", 1), ((1024, 64, 46), "f32", 1),
           ((256, 256, 92), "f16", 0)]
     assert evaluate([f"step_streams({box(*c)})" for c in yes + no]) == [1] * len(yes) + [0] * len(no)
+
+
+def test_16_bit_steps_with_noise_stream_from_the_size_of_the_cache(evaluate):
+    yes = [((256, 256, 80), "f16", 1), ((192, 192, 140), "f16", 1), ((256, 256, 256), "f16", 1)]
+    no = [((256, 256, 72), "f16", 1), ((192, 192, 128), "f16", 1), ((256, 256, 80), "f16", 0), ((256, 128, 80), "f32", 1)]
+    assert evaluate([f"step_streams({box(*c)})" for c in yes + no]) == [1] * len(yes) + [0] * len(no)
+    cases = [(((256, 256, 80), "f16", 1, odd, 0), TILES) for odd in (0, 1)]
+    cases += [(((256, 256, 72), "f16", 1, odd, 0), WAVES) for odd in (0, 1)]
+    assert routes(evaluate, cases) == []
