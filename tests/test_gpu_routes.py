@@ -74,3 +74,16 @@ def test_16_bit_steps_with_noise_at_the_size_of_the_cache(rf, storage, dims):
     a, _ = run(rf, dims, True, 5, **kw)
     b, _ = run(rf, dims, False, 5, **kw)
     assert bool((a == b).all())
+
+
+@pytest.mark.parametrize("storage,kT,dims", [("f16", 0.0, (64, 36, 100)), ("bf16", 0.0, (128, 32, 31)),
+                                             ("f16", 0.0, (1280, 16, 15)), ("f32", 1e-4, (64, 63, 30)),
+                                             ("f32", 1e-4, (192, 32, 32)), ("f32", 0.0, (64, 64, 30))])
+def test_small_boxes_that_stream(rf, storage, kT, dims):
+    kw = dict(storage=storage, kT=kT, tau=0.7, seed=8)
+    if kT == 0.0 and storage != "f32":
+        kw["storage_scale"] = 0.01
+    a, sa = run(rf, dims, True, 5, every=2, **kw)
+    b, sb = run(rf, dims, False, 5, every=2, **kw)
+    assert bool((a == b).all())
+    assert sa["samples"] == sb["samples"] == 3

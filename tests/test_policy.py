@@ -157,3 +157,15 @@ def test_16_bit_steps_with_noise_stream_from_the_size_of_the_cache(evaluate):
     cases = [(((256, 256, 80), "f16", 1, odd, 0), TILES) for odd in (0, 1)]
     cases += [(((256, 256, 72), "f16", 1, odd, 0), WAVES) for odd in (0, 1)]
     assert routes(evaluate, cases) == []
+
+
+def test_small_boxes(evaluate):
+    """Memory-bound steps of 6 to 17 MiB, in FP32 with noise 4 to 22."""
+    yes = [((64, 64, 64), "f16", 0), ((64, 64, 32), "f16", 0), ((1280, 16, 16), "f16", 0), ((4096, 8, 8), "f16", 0),
+           ((64, 64, 28), "f32", 0), ((64, 64, 32), "f32", 1), ((128, 32, 16), "f32", 1), ((192, 64, 16), "f32", 1),
+           ((64, 64, 48), "f32", 1)]
+    no = [((64, 64, 16), "f16", 0), ((64, 64, 88), "f16", 0), ((64, 64, 64), "f16", 1), ((64, 64, 32), "f16", 1),
+          ((2048, 16, 16), "f16", 0), ((63, 64, 64), "f16", 0), ((64, 64, 64), "f32", 0), ((64, 64, 44), "f32", 0),
+          ((64, 64, 64), "f32", 1), ((64, 64, 6), "f32", 1), ((64, 64, 12), "f32", 0), ((63, 64, 32), "f32", 1)]
+    assert evaluate([f"step_streams({box(*c)})" for c in yes + no]) == [1] * len(yes) + [0] * len(no)
+    assert routes(evaluate, [(((1280, 16, 16), "f16", 0, 1, 0), TILES), (((2048, 16, 16), "f16", 0, 1, 0), WAVES)]) == []
