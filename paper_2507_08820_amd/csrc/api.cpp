@@ -196,6 +196,7 @@ static StepBox step_box(const rflbm_lattice* L) {
   b.noise = L->p.kT > 0.0;
   b.row_blocks = L->row_mode;
   b.in_4gib = static_cast<uint64_t>(L->p.nz >> L->L.bz_log) * L->L.plane_pitch < (1ull << 32);
+  b.in_turn = L->turn_bytes != L->L.pop_bytes;
   b.turn_bytes = L->turn_bytes;
   return b;
 }

@@ -27,6 +27,7 @@ struct StepBox {
   bool noise;
   bool row_blocks;       // blocks that follow the rows, not tiles alone
   bool in_4gib;          // populations within 4 GiB
+  bool in_turn;          // stepped in turn with others
   uint64_t turn_bytes;   // populations stepped in turn with these, and these
 };
 
@@ -44,7 +45,8 @@ inline bool memory_bound(const StepBox& b) { return b.value_bytes == 4 || !b.noi
 // (256^3) 599 / 653; FP16 without noise 324 MiB 134 / 137, 864 MiB 303 / 328); beyond
 // 1024 nodes, where odd steps are not in whole rows, beyond 256 MiB (1280 x 64 x 32
 // FP32, 270 MiB, 86 / 96, 1920 x 64 x 22 90 / 98, 1280 x 64 x 64 FP16 without noise 90 / 103),
-// and so 16 bits with noise (256 x 256 x 80 FP16, 270 MiB, 104 / 111, 192 x 192 x 140
+// and so boxes stepped in turn (10 x 64^3 FP32, 270 MiB, 62 / 64 a round of steps) and 16
+// bits with noise (256 x 256 x 80 FP16, 270 MiB, 104 / 111, 192 x 192 x 140
 // 102 / 110, 256 x 256 x 72, 243 MiB, 91 / 85).
 // Memory-bound steps also from 6 to 17 MiB, FP32 with noise from 4 to 22, where the
 // eight L2s (32 MiB) hold the default policy's dirty lines of one step when the next
@@ -60,7 +62,8 @@ inline bool step_streams(const StepBox& b) {
   if (b.nx % 64 != 0) return b.value_bytes == 4 && b.nx % 16 == 0 && b.turn_bytes > kCacheBytes;
   if (memory_bound(b) && b.turn_bytes >= (b.noise ? 4ull : 6ull) << 20 && b.turn_bytes <= (b.noise ? 22ull : 17ull) << 20)
     return true;
-  return b.turn_bytes > (memory_bound(b) && b.nx <= 1024 ? 320ull << 20 : kCacheBytes);
+  const bool whole_rows = memory_bound(b) && b.nx <= 1024;
+  return b.turn_bytes > (whole_rows && !b.in_turn ? 320ull << 20 : kCacheBytes);
 }
 
 // The kernel of one step.

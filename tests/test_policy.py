@@ -88,7 +88,7 @@ def box(dims, storage, noise, row_blocks=1, in_turn=0):
     """StepBox of a box by itself (or of `in_turn` MiB stepped in turn)."""
     size = 27 * dims[0] * dims[1] * dims[2] * BYTES[storage]
     return (f"StepBox{{{dims[0]}u, {BYTES[storage]}u, {str(bool(noise)).lower()}, {str(bool(row_blocks)).lower()}, "
-            f"{str(size < 1 << 32).lower()}, {in_turn * MIB if in_turn else size}ull}}")
+            f"{str(size < 1 << 32).lower()}, {str(in_turn > 0).lower()}, {in_turn * MIB if in_turn else size}ull}}")
 
 
 def routes(evaluate, cases):
@@ -169,3 +169,9 @@ def test_small_boxes(evaluate):
           ((64, 64, 64), "f32", 1), ((64, 64, 6), "f32", 1), ((64, 64, 12), "f32", 0), ((63, 64, 32), "f32", 1)]
     assert evaluate([f"step_streams({box(*c)})" for c in yes + no]) == [1] * len(yes) + [0] * len(no)
     assert routes(evaluate, [(((1280, 16, 16), "f16", 0, 1, 0), TILES), (((2048, 16, 16), "f16", 0, 1, 0), WAVES)]) == []
+
+
+def test_boxes_stepped_in_turn(evaluate):
+    """The size that counts is that of all of them, streamed from 256 MiB."""
+    got = evaluate([f"step_streams({box((64, 64, 64), 'f32', 1, in_turn=mb)})" for mb in (54, 216, 270, 432)])
+    assert got == [0, 0, 1, 1]
