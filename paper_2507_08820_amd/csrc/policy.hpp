@@ -131,9 +131,10 @@ inline bool batch_streams(uint64_t pop_bytes, uint64_t rows) {
 // leaves its partials in the caches for the kernel that adds them: whole sectors are
 // enough (64 of 32^3..96^3 FP16 with statistics every other step 602 / 621, 16 of
 // them 236 / 246; 12 x 100^3 FP16 528 / 473), or replicas so large that this kernel,
-// a block a replica, weighs more than the step (200^3 FP16 859 / 947, 180^3 606 / 695).
+// a block a replica, weighs more than the step (200^3 FP16 859 / 947, 180^3 606 / 695,
+// 144^3 FP32 264 / 292).
 inline bool batch_even_nt(uint64_t pop_bytes, uint64_t rows, bool f32, bool stats, uint64_t largest_nodes) {
-  if (stats && largest_nodes > 1u << 22 && pop_bytes > kCacheBytes) return true;
+  if (stats && pop_bytes > kCacheBytes && largest_nodes > (rows % 32 == 0 ? 1u << 21 : 1u << 22)) return true;
   if (!batch_streams(pop_bytes, rows)) return false;
   return rows % (f32 ? kLineBytes / 2 : kLineBytes) == 0 || (stats && rows % 32 == 0);
 }

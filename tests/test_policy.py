@@ -72,7 +72,8 @@ def test_batches(evaluate):
         ((1304, 64, 1, 0, 96 ** 3, 1), (1, 0)), ((432, 256, 0, 0, 128 ** 3, 0), (1, 0)), ((432, 256, 0, 1, 128 ** 3, 1), (1, 0)),
         ((540, 128, 0, 0, 64 ** 3, 0), (1, 0)), ((1111, 32, 0, 0, 96 ** 3, 0), (0, 0)), ((1111, 32, 0, 1, 96 ** 3, 0), (1, 0)),
         ((1458, 192, 0, 0, 96 ** 3, 1), (0, 0)), ((618, 200, 0, 0, 10 ** 6, 0), (0, 0)), ((618, 200, 0, 1, 10 ** 6, 0), (0, 0)),
-        ((824, 400, 0, 1, 200 ** 3, 0), (1, 0)), ((300, 360, 0, 1, 180 ** 3, 0), (1, 1)), ((141, 260, 0, 0, 455000, 0), (0, 1)),
+        ((824, 400, 0, 1, 200 ** 3, 0), (1, 0)), ((300, 360, 0, 1, 180 ** 3, 0), (1, 1)), ((307, 576, 1, 1, 144 ** 3, 0), (1, 1)),
+        ((307, 576, 1, 0, 144 ** 3, 0), (0, 1)), ((296, 192, 1, 1, 48 ** 3, 0), (0, 1)), ((141, 260, 0, 0, 455000, 0), (0, 1)),
     ]
     got = evaluate([e for (mb, rows, f32, stats, n, tile), _ in cases for e in (
         f"batch_even_nt({mb * MIB}ull, {rows}, {f32}, {stats}, {n})",
