@@ -11,7 +11,6 @@
 #include <cstring>
 #include <new>
 #include <string>
-#include <vector>
 
 #include "../../include/rflbm.h"
 #include "d3q27.hpp"
@@ -671,15 +670,16 @@ int32_t rflbm_sk_nshells(const rflbm_lattice* L) {
   return static_cast<int32_t>(std::llround(h)) + 1;
 }
 
-// exp(-2 pi i t / n), t < n, for the three sides one after another.
-static std::vector<float2> sk_twiddles(const rflbm_params& p) {
-  std::vector<float2> w;
+// exp(-2 pi i t / n), t < n, for the three sides one after another (each at most
+// kFftMaxLength); returns their number.
+static size_t sk_twiddles(const rflbm_params& p, float2 (&w)[3 * kFftMaxLength]) {
+  size_t k = 0;
   for (int32_t n : {p.nx, p.ny, p.nz})
     for (int32_t t = 0; t < n; ++t) {
       const double a = -2.0 * M_PI * t / n;
-      w.push_back(make_float2(static_cast<float>(std::cos(a)), static_cast<float>(std::sin(a))));
+      w[k++] = make_float2(static_cast<float>(std::cos(a)), static_cast<float>(std::sin(a)));
     }
-  return w;
+  return k;
 }
 
 static rflbm_status sk_prepare(rflbm_lattice* L) {
@@ -702,10 +702,11 @@ static rflbm_status sk_prepare(rflbm_lattice* L) {
   RFLBM_HIP(launch_sk_count(L->p.nx, L->p.ny, L->p.nz, L->nshells, L->sk_counts, L->stream));
   RFLBM_HIP(launch_sk_copy(L->sk_counts, L->nshells, L->sk_host + 10 * static_cast<size_t>(L->nshells), L->stream));
   if (L->sk_own) {
-    const std::vector<float2> w = sk_twiddles(L->p);
-    RFLBM_HIP(take(&L->sk_twiddle, w.size() * sizeof(float2)));
+    float2 w[3 * kFftMaxLength];
+    const size_t bytes = sk_twiddles(L->p, w) * sizeof(float2);
+    RFLBM_HIP(take(&L->sk_twiddle, bytes));
     RFLBM_HIP(take(&L->sk_partial, 10 * sizeof(double) * L->nshells * sk_blocks(L->p.nx, L->p.ny, L->p.nz)));
-    RFLBM_HIP(hipMemcpyAsync(L->sk_twiddle, w.data(), w.size() * sizeof(float2), hipMemcpyHostToDevice, L->stream));
+    RFLBM_HIP(hipMemcpyAsync(L->sk_twiddle, w, bytes, hipMemcpyHostToDevice, L->stream));
     RFLBM_HIP(hipStreamSynchronize(L->stream));
   } else {
     RFLBM_HIP(take(&L->sk_fields, 10 * N * sizeof(float)));
