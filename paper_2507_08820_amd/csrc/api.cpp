@@ -682,6 +682,15 @@ static size_t sk_twiddles(const rflbm_params& p, float2 (&w)[3 * kFftMaxLength])
   return k;
 }
 
+// Clears the sums and, in the same stream order, their copy in host memory, which
+// holds what the device holds at every point of the stream (a sample that is
+// captured writes both when its graph runs).
+static rflbm_status sk_clear(rflbm_lattice* L) {
+  RFLBM_HIP(launch_fill_zero(L->sk_sums, 10 * static_cast<size_t>(L->nshells), L->stream));
+  RFLBM_HIP(launch_fill_zero(L->sk_host, 10 * static_cast<size_t>(L->nshells), L->stream));
+  return RFLBM_OK;
+}
+
 static rflbm_status sk_prepare(rflbm_lattice* L) {
   if (L->sk_ready) return RFLBM_OK;
   const uint64_t N = nodes(L);
@@ -697,7 +706,7 @@ static rflbm_status sk_prepare(rflbm_lattice* L) {
   RFLBM_HIP(take(&L->sk_counts, L->nshells * sizeof(unsigned long long)));
   if (!L->sk_host)
     RFLBM_HIP(hipHostMalloc(reinterpret_cast<void**>(&L->sk_host), 11 * L->nshells * sizeof(double), hipHostMallocDefault));
-  RFLBM_HIP(launch_fill_zero(L->sk_sums, 10 * static_cast<size_t>(L->nshells), L->stream));
+  if (rflbm_status s = sk_clear(L)) return s;
   RFLBM_HIP(launch_fill_zero(reinterpret_cast<double*>(L->sk_counts), L->nshells, L->stream));
   RFLBM_HIP(launch_sk_count(L->p.nx, L->p.ny, L->p.nz, L->nshells, L->sk_counts, L->stream));
   RFLBM_HIP(launch_sk_copy(L->sk_counts, L->nshells, L->sk_host + 10 * static_cast<size_t>(L->nshells), L->stream));
@@ -771,7 +780,7 @@ rflbm_status rflbm_get_sk(rflbm_lattice* L, int32_t field, double* shell_sum, in
 rflbm_status rflbm_reset_sk(rflbm_lattice* L) {
   if (rflbm_status s = check_lattice(L)) return s;
   if (!L->sk_ready) return RFLBM_OK;
-  RFLBM_HIP(launch_fill_zero(L->sk_sums, 10 * static_cast<size_t>(L->nshells), L->stream));
+  if (rflbm_status s = sk_clear(L)) return s;
   L->sk_samples = 0;
   return RFLBM_OK;
 }

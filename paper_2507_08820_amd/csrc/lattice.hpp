@@ -82,7 +82,7 @@ struct rflbm_lattice {
   double* sk_partial = nullptr;             // 10 sk_blocks nshells
   double* sk_sums = nullptr;                // 10 nshells
   unsigned long long* sk_counts = nullptr;  // nshells, set once (they depend on the box alone)
-  double* sk_host = nullptr;                // pinned: the sums after each sample, then the counts
+  double* sk_host = nullptr;                // pinned: a copy of the sums, then the counts
   int64_t sk_samples = 0;
   int32_t nshells = 0;
 };

@@ -85,3 +85,38 @@ def test_a_field_that_overflows_leaves_the_others(rf, ora):
         sums = lat.sk(k)[0]
         assert np.isfinite(sums).all() == finite[k], k
     lat.close()
+
+
+@pytest.mark.parametrize("dims", [(16, 12, 10), (1030, 3, 2)])
+def test_a_captured_sample_counts_when_its_graph_runs(rf, dims):
+    """Sums after reset, after the capture of a sample (nothing has run) and after
+    each of three replays, eager work between them."""
+    import torch
+    stream = torch.cuda.Stream()
+    lat = rf.Lattice(dims, kT=1e-4, seed=2, stream=stream)
+    lat.init_thermal()
+    lat.sk_sample()
+    one = [lat.sk(f)[0] for f in range(10)]
+    assert all(s.max() > 0 for s in one)
+    lat.reset_sk()
+    lat.sync()
+    graph = torch.cuda.CUDAGraph()
+    if dims[0] > 1024:  # hipFFT's way: eager samples only
+        lat.sk_sample()
+        for f in range(10):
+            np.testing.assert_allclose(lat.sk(f)[0], one[f], rtol=1e-12)
+        lat.close()
+        return
+    with torch.cuda.graph(graph, stream=stream):
+        lat.sk_sample()
+    for f in range(10):
+        assert not lat.sk(f)[0].any()
+    for k in range(1, 4):
+        with torch.cuda.stream(stream):
+            graph.replay()
+        lat.moments()
+        lat.sync()
+        for f in range(10):
+            # the same products, added in an order of their own
+            np.testing.assert_allclose(lat.sk(f)[0], k * one[f], rtol=1e-12)
+    lat.close()
