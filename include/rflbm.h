@@ -356,8 +356,9 @@ rflbm_status rflbm_batch_time_steps(rflbm_batch* b, int64_t nsteps, double* ms);
  * of every replica region, ENOMEM if that is not available) and restored with
  * the step count afterwards, so the simulation continues bit for bit as if
  * untuned.  With a cache_path (text file, one line per batch signature:
- * device, storage, rounds, replica boxes), a cached choice is applied without
- * timing and new choices are appended.  The graph length is kept. */
+ * device, revision of the kernels, storage, rounds, whether every omega_g = 1,
+ * replica boxes), a cached choice is applied without timing and new choices
+ * are appended.  The graph length is kept. */
 rflbm_status rflbm_batch_autotune(rflbm_batch* b, int32_t trial_steps, const char* cache_path);
 
 /* Diagnostics.
