@@ -21,6 +21,16 @@ namespace rflbm {
 
 namespace {
 
+// Index of this thread in a launch over node_grid (policy.hpp).
+__device__ __forceinline__ uint64_t thread_of_nodes() {
+  return (blockIdx.x + blockIdx.y * kNodeGridX) * 256 + threadIdx.x;
+}
+
+dim3 node_blocks(uint64_t nodes) {
+  const NodeGrid g = node_grid(nodes);
+  return dim3(g.x, g.y);
+}
+
 // f(x, t) of every node, FP64 planar.  Bound by memory: 27 stored words in, 27
 // FP64 values out a node.  One thread per node, whose 27 loads are in flight
 // together; the outputs are streamed (non-temporal), since they are twice to
@@ -34,7 +44,7 @@ __global__ void __launch_bounds__(256) get_pop_kernel(const GatherArgs g, double
   using T = typename C::T;
   const uint32_t N = g.nx * g.ny * g.nz;
   const T* pop = static_cast<const T*>(g.pop);
-  const uint64_t n64 = blockIdx.x * static_cast<uint64_t>(256) + threadIdx.x;
+  const uint64_t n64 = thread_of_nodes();
   if (n64 >= N) return;
   const uint32_t n = static_cast<uint32_t>(n64);
   const Slots<ODD> slot(coords32(n, g), g);
@@ -202,7 +212,7 @@ __global__ void __launch_bounds__(256) init_thermal_kernel(const GatherArgs g, c
   const uint32_t N = g.nx * g.ny * g.nz;
   T* pop = static_cast<T*>(const_cast<void*>(g.pop));
   const double mu = g.rho0 * kT * 3.0;
-  const uint64_t n64 = blockIdx.x * static_cast<uint64_t>(256) + threadIdx.x;
+  const uint64_t n64 = thread_of_nodes();
   if (n64 >= N) return;
   const uint32_t n = static_cast<uint32_t>(n64);
   const Slots<ODD> slot(coords32(n, g), g);
@@ -255,7 +265,7 @@ __global__ void __launch_bounds__(256) moments_kernel(const GatherArgs g, uint32
   using C = Codec<S>;
   using T = typename C::T;
   const T* pop = static_cast<const T*>(g.pop);
-  const uint64_t k = blockIdx.x * static_cast<uint64_t>(256) + threadIdx.x;
+  const uint64_t k = thread_of_nodes();
   if (k >= count) return;
   const Slots<ODD> slot(coords32(static_cast<uint32_t>(n0 + k), g), g);
   float v[kQ];
@@ -372,7 +382,7 @@ template <typename W>
 __global__ void __launch_bounds__(256) swap_parity_kernel(const GatherArgs g) {
   const uint32_t N = g.nx * g.ny * g.nz;
   W* pop = static_cast<W*>(const_cast<void*>(g.pop));
-  const uint64_t n = blockIdx.x * static_cast<uint64_t>(256) + threadIdx.x;
+  const uint64_t n = thread_of_nodes();
   if (n >= N) return;
   const Slots<true> slot(coords32(static_cast<uint32_t>(n), g), g);
   const uint64_t own = slot.row[4] + slot.xs[1];
@@ -420,7 +430,7 @@ hipError_t with_storage(int storage, F f) {
 
 hipError_t launch_get_populations(int storage, const GatherArgs& g, double* dst, hipStream_t s) {
   const uint64_t N = static_cast<uint64_t>(g.nx) * g.ny * g.nz;
-  const dim3 grid(static_cast<uint32_t>((N + 255) / 256)), block(256);
+  const dim3 grid = node_blocks(N), block(256);
   return with_storage(storage, [&](auto st) {
     constexpr int S = decltype(st)::value;
     if (g.odd) hipLaunchKernelGGL((get_pop_kernel<S, true>), grid, block, 0, s, g, dst);
@@ -452,7 +462,7 @@ hipError_t launch_init_thermal(int storage, const GatherArgs& g, const double* r
                                uint32_t key0, uint32_t key1, uint32_t sid, int rounds, double kT,
                                hipStream_t s) {
   const uint64_t N = static_cast<uint64_t>(g.nx) * g.ny * g.nz;
-  const dim3 grid(static_cast<uint32_t>((N + 255) / 256)), block(256);
+  const dim3 grid = node_blocks(N), block(256);
   if (rounds != 7 && rounds != 10) return hipErrorInvalidValue;
   return with_storage(storage, [&](auto st) {
     constexpr int S = decltype(st)::value;
@@ -471,7 +481,7 @@ hipError_t launch_get_moments(int storage, const GatherArgs& g, uint32_t mask, f
 hipError_t launch_get_moments_range(int storage, const GatherArgs& g, uint32_t mask, uint64_t n0,
                                     uint64_t count, float* dst, uint64_t pitch, hipStream_t s) {
   if (count == 0) return hipSuccess;
-  const dim3 grid(static_cast<uint32_t>((count + 255) / 256)), block(256);
+  const dim3 grid = node_blocks(count), block(256);
   const uint64_t pop_bytes = static_cast<uint64_t>(kQ) * g.nx * g.ny * g.nz * storage_bytes(storage);
   const bool nt = read_streams(static_cast<uint64_t>(g.nx) * storage_bytes(storage), pop_bytes, g.odd != 0);
   return with_storage(storage, [&](auto st) {
@@ -504,7 +514,7 @@ hipError_t launch_rng_normals(uint32_t key0, uint32_t key1, uint32_t stream_id, 
 
 hipError_t launch_swap_parity(int storage, const GatherArgs& g, hipStream_t s) {
   const uint64_t N = static_cast<uint64_t>(g.nx) * g.ny * g.nz;
-  const dim3 grid(static_cast<uint32_t>((N + 255) / 256)), block(256);
+  const dim3 grid = node_blocks(N), block(256);
   if (storage_bytes(storage) == 4) hipLaunchKernelGGL(swap_parity_kernel<uint32_t>, grid, block, 0, s, g);
   else hipLaunchKernelGGL(swap_parity_kernel<uint16_t>, grid, block, 0, s, g);
   return hipGetLastError();

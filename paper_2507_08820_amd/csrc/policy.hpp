@@ -7,6 +7,18 @@ namespace rflbm {
 
 constexpr uint32_t kFftMaxLength = 1024;  // of the transforms in LDS (fft.hpp)
 
+// Grid of 256-thread blocks, one thread a node: block x + y kNodeGridX covers the nodes
+// from 256 times that.  A launch takes fewer than 2^32 threads along an axis, so the
+// largest boxes (below 2^32 nodes) go over two.
+constexpr uint64_t kNodeGridX = 1ull << 23;
+struct NodeGrid {
+  uint32_t x, y;
+};
+inline NodeGrid node_grid(uint64_t nodes) {
+  const uint64_t blocks = (nodes + 255) / 256, x = blocks < kNodeGridX ? blocks : kNodeGridX;
+  return NodeGrid{static_cast<uint32_t>(x), static_cast<uint32_t>((blocks + x - 1) / x)};
+}
+
 constexpr uint32_t kLineBytes = 128;           // cache line
 constexpr uint64_t kCacheBytes = 256ull << 20;  // memory-side cache of an MI355X (Infinity Cache)
 

@@ -176,3 +176,11 @@ def test_boxes_stepped_in_turn(evaluate):
     """The size that counts is that of all of them, streamed from 256 MiB."""
     got = evaluate([f"step_streams({box((64, 64, 64), 'f32', 1, in_turn=mb)})" for mb in (54, 216, 270, 432)])
     assert got == [0, 0, 1, 1]
+
+
+def test_one_thread_a_node(evaluate):
+    """Every box below 2^32 nodes in a launch that HIP takes (fewer than 2^32 threads
+    along an axis)."""
+    for n in (1, 255, 256, 257, 512 ** 3, 2 ** 31, 2 ** 31 + 1, 2 ** 32 - 257, 2 ** 32 - 256, 2 ** 32 - 255, 2 ** 32 - 1):
+        x, y = evaluate([f"node_grid({n}ull).x", f"node_grid({n}ull).y"])
+        assert x * 256 < 2 ** 32 and y < 2 ** 16 and x * y * 256 >= n and x * (y - 1) * 256 < n
