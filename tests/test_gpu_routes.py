@@ -3,6 +3,8 @@ special lengths store the bits of the tiled kernel."""
 import numpy as np
 import pytest
 
+import workloads as wl
+
 pytestmark = pytest.mark.gpu
 
 
@@ -87,3 +89,51 @@ def test_small_boxes_that_stream(rf, storage, kT, dims):
     b, sb = run(rf, dims, False, 5, every=2, **kw)
     assert bool((a == b).all())
     assert sa["samples"] == sb["samples"] == 3
+
+
+# recursive ghosts are a kernel of their own in every block shape: flat, rows, waves (16
+# bits with noise; odd steps of long rows), and the tiles of all of them
+@pytest.mark.parametrize("storage,kT", [("f32", 1e-4), ("f32", 0.0), ("f16", 1e-4), ("bf16", 1e-4)])
+@pytest.mark.parametrize("dims", [(17, 19, 23), (65, 4, 16), (130, 9, 5), (64, 3, 2), (192, 5, 4), (1088, 2, 2)])
+def test_recursive_ghosts_in_every_block_shape(rf, dims, storage, kT):
+    kw = dict(storage=storage, kT=kT, tau=0.7, tau_bulk=1.2, model="rec", tau_ghost=list(np.linspace(0.6, 1.8, 17)), seed=9)
+    a, sa = run(rf, dims, True, 7, every=3, **kw)
+    b, sb = run(rf, dims, False, 7, every=3, **kw)
+    assert bool((a == b).all())
+    assert sa["samples"] == sb["samples"] == 3
+
+
+# the tiled kernel, which rows that do not fill waves reach beyond 4 GiB and with row
+# blocks off
+TILED = {
+    "ragged_130x9x5": ((130, 9, 5), dict(kT=1e-4, tau=0.55, seed=11)),
+    "ragged_300x3x4": ((300, 3, 4), dict(kT=1e-4, tau=0.6, seed=12)),
+    "odd_17x19x23_mrt": ((17, 19, 23), dict(kT=1e-5, tau=0.8, tau_bulk=1.0, tau_ghost=list(np.linspace(0.7, 1.6, 17)),
+                                            seed=7, stream_id=3)),
+    "wide_1088x2x2": ((1088, 2, 2), dict(kT=1e-4, tau=0.65, seed=17)),
+    "rec_17x19x23": ((17, 19, 23), dict(kT=1e-4, tau=0.7, tau_bulk=1.2, model="rec",
+                                        tau_ghost=list(np.linspace(0.55, 1.9, 17)), seed=20)),
+    "rec_kT0_33x7x6": ((33, 7, 6), dict(kT=0.0, tau=0.9, model="rec", tau_ghost=1.5)),
+    "rec_128x5x3": ((128, 5, 3), dict(kT=1e-4, tau=0.6, model="rec", tau_ghost=0.8, seed=21)),
+}
+
+
+@pytest.mark.parametrize("case", list(TILED))
+def test_tiled_trajectories_match_the_oracle(rf, ora, case):
+    """max |f_gpu - f_oracle| / (w_i rho0) <= 1e-5 at every step, as for every other
+    kernel (the bar of the method's specification)."""
+    dims, kw = TILED[case]
+    rho, u = wl.random_velocity(dims, 31)
+    w = ora.tables()["w"][:, None]
+    ref = ora.init_equilibrium(dims, rho, u)
+    ref = ref + 1e-3 * w * wl.normal_array(ref.shape, 32)
+    lat = rf.Lattice(dims, **kw)
+    lat.set_row_blocks(False)
+    lat.set_populations(ref)
+    p = ora.make_params(kT=kw["kT"], tau_shear=kw["tau"], tau_bulk=kw.get("tau_bulk"), tau_ghost=kw.get("tau_ghost", 1.0),
+                        seed=kw.get("seed", 1), stream_id=kw.get("stream_id", 0), rounds=7, model=kw.get("model", "reg"))
+    for t in range(40):
+        lat.step(1)
+        ref = ora.step(p, dims, ref, t)
+        assert np.max(np.abs(lat.populations().cpu().numpy() - ref) / w) <= 1e-5, t + 1
+    lat.close()

@@ -120,3 +120,27 @@ def test_a_captured_sample_counts_when_its_graph_runs(rf, dims):
             # the same products, added in an order of their own
             np.testing.assert_allclose(lat.sk(f)[0], k * one[f], rtol=1e-12)
     lat.close()
+
+
+@pytest.mark.parametrize("dims", [(128, 64, 128), (90, 96, 100), (64, 130, 61), (100, 70, 59)])
+def test_blocks_that_walk_several_tiles(rf, ora, dims):
+    """More tiles of columns than the 51 blocks a field of the last pass: tiles met in
+    its loop, a partial one last, blocks with a tile fewer; z sides of powers of two,
+    of small radices and prime."""
+    nx, ny, nz = dims
+    columns = 1
+    while columns < 64 and nz * 2 * columns <= 4096:
+        columns *= 2
+    assert -(-ny * (nx // 2 + 1) // columns) > 51
+    lat = rf.Lattice(dims, kT=1e-4, tau=0.8, seed=9)
+    lat.init_thermal()
+    lat.step(1)
+    fields = lat.moments().cpu().numpy().astype(np.float64)
+    fields[0] = density_deviation(lat.populations().cpu().numpy(), ora.tables()["w"])
+    lat.sk_sample()
+    shell = shells(dims)
+    for f in range(10):
+        sums, counts, _ = lat.sk(f)
+        np.testing.assert_array_equal(counts, np.bincount(shell[1:], minlength=len(sums)))
+        check_field(sums, fields[f], dims, shell)
+    lat.close()
