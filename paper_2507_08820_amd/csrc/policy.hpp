@@ -60,11 +60,12 @@ inline bool memory_bound(const StepBox& b) { return b.value_bytes == 4 || !b.noi
 // and so boxes stepped in turn (10 x 64^3 FP32, 270 MiB, 62 / 64 a round of steps) and 16
 // bits with noise (256 x 256 x 80 FP16, 270 MiB, 104 / 111, 192 x 192 x 140
 // 102 / 110, 256 x 256 x 72, 243 MiB, 91 / 85).
-// Memory-bound steps also from 6 to 17 MiB, FP32 with noise from 4 to 22, where the
+// Memory-bound steps also from 6 to 18.5 MiB, FP32 with noise from 4 to 24, where the
 // eight L2s (32 MiB) hold the default policy's dirty lines of one step when the next
 // wants them on other XCDs (FP32 with noise 64 x 64 x 20 5.8 / 6.1, 64 x 64 x 32 6.3 / 7.1, 64
 // x 64 x 48 7.5 / 8.5; 64 x 64 x 6, 3 MiB, 4.8 / 4.7, 64 x 64 x 60, 25 MiB, 9.3 / 9.1, 64^3 10.3 / 9.5;
-// without noise 64 x 64 x 28 5.7 / 5.8, 64 x 64 x 44, 19 MiB, 7.1 / 6.9; FP16 without noise
+// without noise 64 x 64 x 28 5.7 / 5.8, 320 x 21 x 25, 17.3 MiB, statistics every fifth step,
+// 9.5 / 11.1, 64 x 64 x 44, 19 MiB, 7.1 / 6.9; FP16 without noise
 // 64^3 7.5 / 7.6, 1280 x 16 x 16 8.2 / 8.8, 4096 x 8 x 8 7.3 / 8.4; 4096 x 16 x 16, 54 MiB, 21 / 17).
 // Flat blocks: FP32 rows of whole or half lines beyond 256 MiB (160 x 160 x 100, 264 MiB,
 // 85 / 95, 96 x 256 x 256 235 / 265, 416 x 200 x 200 647 / 688, 16 x 700 x 700 321 / 338);
@@ -72,7 +73,7 @@ inline bool memory_bound(const StepBox& b) { return b.value_bytes == 4 || !b.noi
 // 300 FP16 201 / 196).
 inline bool step_streams(const StepBox& b) {
   if (b.nx % 64 != 0) return b.value_bytes == 4 && b.nx % 16 == 0 && b.turn_bytes > kCacheBytes;
-  if (memory_bound(b) && b.turn_bytes >= (b.noise ? 4ull : 6ull) << 20 && b.turn_bytes <= (b.noise ? 22ull : 17ull) << 20)
+  if (memory_bound(b) && b.turn_bytes >= (b.noise ? 4ull : 6ull) << 20 && 2 * b.turn_bytes <= (b.noise ? 48ull : 37ull) << 20)
     return true;
   const bool whole_rows = memory_bound(b) && b.nx <= 1024;
   return b.turn_bytes > (whole_rows && !b.in_turn ? 320ull << 20 : kCacheBytes);
