@@ -216,6 +216,7 @@ StepArgs step_args(const rflbm_lattice* L) {
   a.bz_log = L->L.bz_log;
   a.plane_pitch = L->L.plane_pitch;
   a.streams = step_streams(step_box(L)) ? 1u : 0u;
+  a.few_waves = step_few_waves(step_box(L)) ? 1u : 0u;
   a.tiles_x = (p.nx + L->launch.bx - 1) / L->launch.bx;
   a.tiles_y = (p.ny + L->launch.by - 1) / L->launch.by;
   a.ntiles = a.tiles_x * a.tiles_y * static_cast<uint32_t>(p.nz);

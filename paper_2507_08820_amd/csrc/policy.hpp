@@ -79,6 +79,17 @@ inline bool step_streams(const StepBox& b) {
   return b.turn_bytes > (whole_rows && !b.in_turn ? 320ull << 20 : kCacheBytes);
 }
 
+// True when the steps in rows and in waves keep to about half of the 32 waves a CU
+// holds: FP32 beyond the memory-side cache, where fewer accesses in flight reach 1 to
+// 4 % more of memory's rate (figures at step_row_lds, step.hip).  Not in the cache or in
+// 16 bits (64^3 8.4 us a step, with 20 waves 9.1; 192^3 FP16 294 / 309, 320 x 256 x 200
+// FP16 330 / 347), nor rows of an odd number of waves from five on (320 x 256 x 200 with
+// statistics 624 / 640, 1088 x 64 x 64 158.6 / 160.8, 960 x 60 x 61 140.2 / 140.5).
+inline bool step_few_waves(const StepBox& b) {
+  return b.value_bytes == 4 && (b.nx % 128 == 0 || b.nx == 64 || b.nx == 192) && b.turn_bytes > kCacheBytes &&
+         step_streams(b);
+}
+
 // The kernel of one step.
 //
 // Rows that do not fill waves, within 4 GiB: flat blocks, which leave no lane idle

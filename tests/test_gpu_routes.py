@@ -70,6 +70,20 @@ def test_rows_longer_than_a_block(rf, storage, dims, kT):
     assert bool((a == b).all())
 
 
+# every count of blocks a CU that whole rows are held to beyond the cache
+@pytest.mark.parametrize("kT", [1e-4, 0.0])
+@pytest.mark.parametrize("nx", [64, 128, 192, 256, 384, 512, 640, 768, 896, 1024])
+def test_rows_with_fewer_waves_beyond_the_cache(rf, nx, kT):
+    kw = dict(storage="f32", kT=kT, tau=0.7, seed=8, model="bgk")
+    dims = (nx, 47, 3200000 // (47 * nx))
+    a, sa = run(rf, dims, True, 4, every=3, **kw)
+    b, sb = run(rf, dims, False, 4, every=3, **kw)
+    assert bool((a == b).all())
+    n = sa["nodes"] * sa["samples"]
+    for k in ("sum_drho2", "sum_j2", "sum_u2", "sum_pi2"):
+        assert np.all(np.abs(sa[k] - sb[k]) <= n * 2.0 ** -53 * np.abs(sa[k])), k
+
+
 @pytest.mark.parametrize("storage,dims", [("f16", (256, 250, 80)), ("bf16", (192, 190, 142))])
 def test_16_bit_steps_with_noise_at_the_size_of_the_cache(rf, storage, dims):
     kw = dict(storage=storage, kT=1e-4, tau=0.7, seed=7)

@@ -160,6 +160,20 @@ def test_16_bit_steps_with_noise_stream_from_the_size_of_the_cache(evaluate):
     assert routes(evaluate, cases) == []
 
 
+def test_fewer_waves(evaluate):
+    """FP32 steps in rows and waves that stream from memory; not in the cache, in 16
+    bits, or in rows of 5, 7, 9, ... waves."""
+    yes = [((64, 512, 512), 0), ((128, 301, 299), 0), ((192, 256, 300), 0), ((256, 256, 256), 0), ((384, 207, 247), 0),
+           ((512, 256, 128), 0), ((640, 200, 160), 0), ((1024, 61, 53), 0), ((1280, 64, 64), 0), ((4096, 32, 24), 0),
+           ((64, 64, 64), 270)]
+    no = [((320, 256, 200), 0), ((576, 99, 111), 0), ((960, 60, 61), 0), ((1088, 64, 64), 0), ((128, 128, 128), 0),
+          ((64, 64, 64), 0), ((64, 64, 32), 0), ((130, 150, 150), 0), ((192, 100, 150), 0)]
+    for noise in (0, 1):
+        got = evaluate([f"step_few_waves({box(d, 'f32', noise, in_turn=t)})" for d, t in yes + no])
+        assert got == [1] * len(yes) + [0] * len(no)
+        assert not any(evaluate([f"step_few_waves({box(d, 'f16', noise)})" for d, _ in yes]))
+
+
 def test_small_boxes(evaluate):
     """Memory-bound steps of 6 to 18.5 MiB, in FP32 with noise 4 to 24."""
     yes = [((64, 64, 64), "f16", 0), ((64, 64, 32), "f16", 0), ((1280, 16, 16), "f16", 0), ((4096, 8, 8), "f16", 0),
