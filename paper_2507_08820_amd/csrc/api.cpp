@@ -216,7 +216,9 @@ StepArgs step_args(const rflbm_lattice* L) {
   a.bz_log = L->L.bz_log;
   a.plane_pitch = L->L.plane_pitch;
   a.streams = step_streams(step_box(L)) ? 1u : 0u;
-  a.few_waves = step_few_waves(step_box(L)) ? 1u : 0u;
+  const StepBlocks held = step_blocks(step_box(L));
+  a.wave_blocks = held.waves;
+  a.row_blocks = held.rows;
   a.tiles_x = (p.nx + L->launch.bx - 1) / L->launch.bx;
   a.tiles_y = (p.ny + L->launch.by - 1) / L->launch.by;
   a.ntiles = a.tiles_x * a.tiles_y * static_cast<uint32_t>(p.nz);

@@ -45,7 +45,7 @@ struct StepArgs {
   uint32_t by_log, bz_log;  // log2 of the brick shape By x Bz (0, 0: plain layout)
   uint64_t plane_pitch;  // bytes from one brick row (Bz z planes) to the next (P)
   uint32_t streams;      // 1: non-temporal population accesses (step_streams, policy.hpp)
-  uint32_t few_waves;    // 1: blocks reserve LDS, for fewer waves a CU (step_few_waves)
+  uint32_t wave_blocks, row_blocks;  // a CU is held to, 0: as many as fit (step_blocks, policy.hpp)
   uint32_t tiles_x;      // tiles along x (tile = blockDim.x x blockDim.y nodes of one z plane)
   uint32_t tiles_y;      // tiles along y
   uint32_t ntiles;       // tiles_x * tiles_y * nz

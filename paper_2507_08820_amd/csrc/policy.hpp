@@ -79,15 +79,29 @@ inline bool step_streams(const StepBox& b) {
   return b.turn_bytes > (whole_rows && !b.in_turn ? 320ull << 20 : kCacheBytes);
 }
 
-// True when the steps in rows and in waves keep to about half of the 32 waves a CU
-// holds: FP32 beyond the memory-side cache, where fewer accesses in flight reach 1 to
-// 4 % more of memory's rate (figures at step_row_lds, step.hip).  Not in the cache or in
-// 16 bits (64^3 8.4 us a step, with 20 waves 9.1; 192^3 FP16 294 / 309, 320 x 256 x 200
-// FP16 330 / 347), nor rows of an odd number of waves from five on (320 x 256 x 200 with
-// statistics 624 / 640, 1088 x 64 x 64 158.6 / 160.8, 960 x 60 x 61 140.2 / 140.5).
-inline bool step_few_waves(const StepBox& b) {
-  return b.value_bytes == 4 && (b.nx % 128 == 0 || b.nx == 64 || b.nx == 192) && b.turn_bytes > kCacheBytes &&
-         step_streams(b);
+// Blocks a CU is held to by steps in waves and in rows, 0: as many as fit (32 waves).
+// Memory-bound steps that stream from memory reach 1 to 4 % more of its rate with
+// about half the waves, hence fewer accesses in flight (us a step with 32 / fewer).
+// FP32, 20 blocks of a wave and rows of 14 to 20 waves: BGK 384 x 207 x 247 769 / 742,
+// 512 x 256 x 128 618 / 597 and with statistics 635 / 601, 128 x 256 x 512 629 / 608, 1024 x 128 x
+// 128 635 / 623; two blocks at least (one: 1024 x 128 x 128 644, 768 x 200 x 150 864 / 902).
+// Rows of an odd number of waves gain up to seven waves, without noise up to nine
+// (448 x 200 x 200 with statistics 683 / 660, 320 x 256 x 200 620 / 611, but with noise 617 / 637;
+// 960 x 60 x 61 139.2 / 139.7, 1088 x 64 x 64 159 / 161).
+// 16 bits without noise, 16 blocks of a wave and rows of up to three waves at 18 to 20
+// (BF16 BGK 192 x 256 x 300 276 / 269 in waves, 276 / 272 in rows, 320 x 226 x 191 265 / 258;
+// rows of 16 waves 128 x 299 x 397 with statistics 288 / 298, of 384 nodes 372 / 461).
+// In the cache and with noise in 16 bits fewer waves lose (64^3 8.4 / 9.1, 192^3 FP16 294 /
+// 309, 320 x 256 x 200 FP16 330 / 347).
+struct StepBlocks {
+  uint32_t waves, rows;
+};
+inline StepBlocks step_blocks(const StepBox& b) {
+  if (!memory_bound(b) || b.nx % 64 != 0 || b.turn_bytes <= kCacheBytes || !step_streams(b)) return {0, 0};
+  const uint32_t waves = b.nx / 64;
+  if (b.value_bytes != 4) return {16, waves <= 3 ? 20 / waves : 0};
+  if (waves % 2 == 1 && waves >= 5 && (b.noise ? waves != 7 : waves > 9)) return {0, 0};
+  return {20, waves < 8 ? 16 / waves : 2};
 }
 
 // The kernel of one step.

@@ -30,6 +30,7 @@
 // reads the setting per replica).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "d3q27.hpp"
@@ -638,33 +639,29 @@ hipError_t launch_flat_s(bool odd, int rounds, bool stats, const StepArgs& a, ui
   return stats ? launch_flat_r<S, false, true>(rounds, a, grid, s) : launch_flat_r<S, false, false>(rounds, a, grid, s);
 }
 
-// Bytes of LDS that a block reserves, without using them, so that a
-// CU holds fewer blocks: one-wave blocks at 20 a CU, rows at 14 to 20 waves and no
-// fewer than two blocks.  Beyond the memory-side cache the registers' 32 waves a CU
-// lose to that (step_few_waves, policy.hpp).  FP32, us a step with 32 / fewer: BGK 384 x 207 x 247 769
-// / 742, 512 x 256 x 128 618 / 597 and with statistics 635 / 601, 128 x 256 x 512 629 / 608,
-// 1024 x 128 x 128 635 / 623.  One block a CU loses: 1024 x 128 x 128 644, 768 x 200 x 150
-// 864 -> 902.
+// LDS that a block with `own` bytes of its own reserves, without using it, so that a CU
+// holds `blocks` blocks (step_blocks, policy.hpp); two fit with 64 KiB each, three do not.
 constexpr uint32_t kCuLds = 160 * 1024;
-constexpr uint32_t kRowLds = 4 * 1024;  // no less than a row block's own
-uint32_t step_wave_lds(const StepArgs& a) { return a.few_waves ? kCuLds / 20 : 0; }
-uint32_t step_row_lds(const StepArgs& a) {
-  if (!a.few_waves) return 0;
-  const uint32_t blocks = 16 / (a.nx / 64);
-  return (blocks > 2 ? kCuLds / blocks : 64 * 1024) - kRowLds;  // 64 KiB: two blocks fit
+uint32_t unused_lds(uint32_t blocks, uint32_t own) {
+  return blocks == 0 ? 0 : std::min(kCuLds / blocks, 64u * 1024) / 512 * 512 - own;
 }
 
 template <int S, int R, bool ST, bool ODD, bool NT>
 void launch_row_g(const StepArgs& a, dim3 g, dim3 blk, hipStream_t s) {
+  constexpr uint32_t own = 4 * kMaxRowWaves * ((ODD ? 2 * 18 : 0) + (ST ? kNumStats : 0));
+  // with statistics in 16 bits all that fit: BF16 BGK 192 x 256 x 300 294 us a step, held to
+  // six blocks a CU 327
+  const uint32_t lds = unused_lds(ST && S != kF32 ? 0 : a.row_blocks, own);
   by_ghosts(a, [&](auto gh) {
-    hipLaunchKernelGGL((step_row_kernel<S, R, decltype(gh)::value, ST, ODD, NT>), g, blk, step_row_lds(a), s, a);
+    hipLaunchKernelGGL((step_row_kernel<S, R, decltype(gh)::value, ST, ODD, NT>), g, blk, lds, s, a);
   });
 }
 
 template <int S, int R, bool ODD, bool NT>
 void launch_wave_g(const StepArgs& a, dim3 g, hipStream_t s) {
   by_ghosts(a, [&](auto gh) {
-    hipLaunchKernelGGL((step_wave_kernel<S, R, decltype(gh)::value, ODD, NT>), g, dim3(64), step_wave_lds(a), s, a);
+    hipLaunchKernelGGL((step_wave_kernel<S, R, decltype(gh)::value, ODD, NT>), g, dim3(64),
+                       unused_lds(a.wave_blocks, 0), s, a);
   });
 }
 

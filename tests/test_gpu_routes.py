@@ -70,12 +70,17 @@ def test_rows_longer_than_a_block(rf, storage, dims, kT):
     assert bool((a == b).all())
 
 
-# every count of blocks a CU that whole rows are held to beyond the cache
-@pytest.mark.parametrize("kT", [1e-4, 0.0])
-@pytest.mark.parametrize("nx", [64, 128, 192, 256, 384, 512, 640, 768, 896, 1024])
-def test_rows_with_fewer_waves_beyond_the_cache(rf, nx, kT):
-    kw = dict(storage="f32", kT=kT, tau=0.7, seed=8, model="bgk")
-    dims = (nx, 47, 3200000 // (47 * nx))
+# every count of blocks that a CU is held to beyond the cache
+HELD = [("f32", nx, kT) for nx in (64, 128, 192, 256, 320, 384, 448, 512, 640, 768, 896, 1024) for kT in (1e-4, 0.0)]
+HELD += [(s, nx, 0.0) for s, nx in (("f16", 64), ("bf16", 128), ("f16", 192), ("bf16", 256), ("f16", 1024))]
+
+
+@pytest.mark.parametrize("storage,nx,kT", HELD)
+def test_rows_with_fewer_waves_beyond_the_cache(rf, storage, nx, kT):
+    kw = dict(storage=storage, kT=kT, tau=0.7, seed=8, model="bgk")
+    if storage != "f32":
+        kw["storage_scale"] = 0.01
+    dims = (nx, 47, (3200000 if storage == "f32" else 6400000) // (47 * nx))
     a, sa = run(rf, dims, True, 4, every=3, **kw)
     b, sb = run(rf, dims, False, 4, every=3, **kw)
     assert bool((a == b).all())

@@ -160,18 +160,24 @@ def test_16_bit_steps_with_noise_stream_from_the_size_of_the_cache(evaluate):
     assert routes(evaluate, cases) == []
 
 
-def test_fewer_waves(evaluate):
-    """FP32 steps in rows and waves that stream from memory; not in the cache, in 16
-    bits, or in rows of 5, 7, 9, ... waves."""
-    yes = [((64, 512, 512), 0), ((128, 301, 299), 0), ((192, 256, 300), 0), ((256, 256, 256), 0), ((384, 207, 247), 0),
-           ((512, 256, 128), 0), ((640, 200, 160), 0), ((1024, 61, 53), 0), ((1280, 64, 64), 0), ((4096, 32, 24), 0),
-           ((64, 64, 64), 270)]
-    no = [((320, 256, 200), 0), ((576, 99, 111), 0), ((960, 60, 61), 0), ((1088, 64, 64), 0), ((128, 128, 128), 0),
-          ((64, 64, 64), 0), ((64, 64, 32), 0), ((130, 150, 150), 0), ((192, 100, 150), 0)]
-    for noise in (0, 1):
-        got = evaluate([f"step_few_waves({box(d, 'f32', noise, in_turn=t)})" for d, t in yes + no])
-        assert got == [1] * len(yes) + [0] * len(no)
-        assert not any(evaluate([f"step_few_waves({box(d, 'f16', noise)})" for d, _ in yes]))
+def test_blocks_a_cu_is_held_to(evaluate):
+    """Memory-bound steps that stream from memory; not in the cache, with noise in 16
+    bits, or in long rows of an odd number of waves."""
+    f32 = [((64, 512, 512), 20, 16), ((128, 301, 299), 20, 8), ((192, 256, 300), 20, 5), ((256, 256, 256), 20, 4),
+           ((384, 207, 247), 20, 2), ((448, 111, 87), 20, 2), ((512, 256, 128), 20, 2), ((640, 200, 160), 20, 2),
+           ((1024, 61, 53), 20, 2), ((1280, 64, 64), 20, 2), ((4096, 32, 24), 20, 2)]
+    free = [(704, 100, 120), (960, 60, 61), (1088, 64, 64), (128, 128, 128), (64, 64, 64), (64, 64, 32), (130, 150, 150),
+            (192, 100, 150)]
+    f16 = [((64, 512, 512), 16, 20), ((128, 299, 397), 16, 10), ((192, 256, 300), 16, 6), ((256, 256, 256), 16, 0),
+           ((384, 207, 247), 16, 0), ((1280, 100, 100), 16, 0), ((2048, 64, 96), 16, 0)]
+    cases = [((d, "f32", noise), w, r) for d, w, r in f32 for noise in (0, 1)]
+    cases += [((d, "f32", noise), 0, 0) for d in free for noise in (0, 1)] + [((d, "f16", 0), 0, 0) for d in free[3:]]
+    cases += [(((320, 256, 200), "f32", 0), 20, 3), (((576, 150, 150), "f32", 0), 20, 2),
+              (((320, 256, 200), "f32", 1), 0, 0), (((576, 150, 150), "f32", 1), 0, 0)]
+    cases += [((d, "f16", 0), w, r) for d, w, r in f16] + [((d, "f16", 1), 0, 0) for d, _, _ in f16]
+    got = evaluate([f"step_blocks({box(*c)}).{k}" for c, _, _ in cases for k in ("waves", "rows")])
+    assert [c for c, w, r in zip(cases, got[::2], got[1::2]) if (w, r) != c[1:]] == []
+    assert evaluate([f"step_blocks({box((64, 64, 64), 'f32', 1, in_turn=270)}).waves"]) == [20]
 
 
 def test_small_boxes(evaluate):
