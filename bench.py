@@ -31,7 +31,7 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "step_f32_512_traffic.txt")
 KERNEL_SOURCES = ["paper_2507_08820_amd/csrc/step.hip", "paper_2507_08820_amd/csrc/node_body.inc",
                   "paper_2507_08820_amd/csrc/node_collide.inc", "paper_2507_08820_amd/csrc/d3q27.hpp", "paper_2507_08820_amd/csrc/philox.hpp",
                   "paper_2507_08820_amd/csrc/storage.hpp", "paper_2507_08820_amd/csrc/kernels.hpp",
-                  "paper_2507_08820_amd/csrc/fastdiv.hpp"]
+                  "paper_2507_08820_amd/csrc/fastdiv.hpp", "paper_2507_08820_amd/csrc/policy.hpp"]
 
 
 def kernel_hash() -> str:

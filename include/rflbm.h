@@ -259,9 +259,10 @@ rflbm_status rflbm_reset_sk(rflbm_lattice* lat);
 
 /* Launch shape of the step kernel: blocks of bx x (256 / bx) nodes of one
  * z plane, bx in {64, 128, 256}; xcd_remap != 0 hands each of the 8 XCDs a
- * contiguous range of tiles (neighbouring tiles then share an L2).  Any shape
- * gives the same results bit for bit.  rflbm_create picks the widest bx that
- * the box's x extent fills. */
+ * contiguous range of blocks (neighbours then share an L2).  Any shape gives the
+ * same results bit for bit.  rflbm_create picks the widest bx that the box's x
+ * extent fills.  bx shapes the tiled steps only: all with row blocks off, else
+ * those that rflbm_set_row_blocks names; xcd_remap acts on every step. */
 rflbm_status rflbm_set_launch(rflbm_lattice* lat, int32_t bx, int32_t xcd_remap);
 rflbm_status rflbm_get_launch(const rflbm_lattice* lat, int32_t* bx, int32_t* xcd_remap);
 
@@ -274,12 +275,18 @@ rflbm_status rflbm_get_launch(const rflbm_lattice* lat, int32_t* bx, int32_t* xc
  *     and every load and store covers whole aligned cache lines;
  *   other nx, populations below 4 GiB: every step runs in blocks of
  *     consecutive nodes, row after row, so that rows need not fill waves.
- * The 16-bit steps with noise keep the tiled kernel for large boxes with nx a
- * multiple of 256, and for statistics; everything else, and all steps when
- * disabled, keep the tiled shape of rflbm_set_launch.  Results are bit for bit
- * the same either way.  Enabled by rflbm_create.  rflbm_get_row_blocks sets
- * *active to 1 when the next odd step runs in whole rows (it depends on
- * storage, k_BT and nx). */
+ * Tiles of rflbm_set_launch, the shape of all steps when disabled, stay where they
+ * measured faster:
+ *   16 bits with noise: statistics steps, and every step of boxes beyond 256
+ *     MiB of populations with nx a multiple of 256;
+ *   bound by bandwidth, nx a multiple of 64 beyond 1024: statistics steps, and odd
+ *     steps with nx a multiple of 128 (FP32) or, beyond 256 MiB, of 256 (16 bits);
+ *   other nx beyond 256 MiB: nx = 33..63 (16 bits: 45..63), and FP32 rows of 480 or
+ *     more nodes, a multiple of 16, that fill 15 of 16 lanes of tiles of 256;
+ *   other nx, populations of 4 GiB and more.
+ * Results are bit for bit the same either way.  Enabled by rflbm_create.
+ * rflbm_get_row_blocks sets *active to 1 when the next odd step runs in whole rows
+ * (it depends on storage, k_BT and nx). */
 rflbm_status rflbm_set_row_blocks(rflbm_lattice* lat, int32_t enable);
 rflbm_status rflbm_get_row_blocks(const rflbm_lattice* lat, int32_t* active);
 

@@ -280,9 +280,10 @@ __global__ void __launch_bounds__(kBlock) step_kernel(const StepArgs a) {
 // -> 17.6; 96^3 FP32 36.4 -> 29.8, FP16 27.6 -> 21.0; 200^3 FP32 431 -> 341;
 // 300 x 280 x 260 BF16 795 -> 533.  A block is one wave, so that a small box
 // spreads over more CUs: 17 x 19 x 23 FP32 4.4 us, in blocks of 256 5.6, tiled
-// 5.0; large boxes do not care, except with statistics, whose staging and
-// partials weigh more (us per step in blocks of 64 / 256: 16^3 5.3 / 6.1, 17 x 19
-// x 23 5.4 / 6.6, 48^3 FP16 11.8 / 8.1, 100^3 49 / 40; flat_block).
+// 5.0; large boxes do not care, except with statistics: each block writes its
+// partials and holds the staging of 256 nodes (24 KB of LDS), so that six one-wave
+// blocks fill a CU (us per step in blocks of 64 / 256: 16^3 5.3 / 6.1, 17 x 19 x 23
+// 5.4 / 6.6, 48^3 FP16 11.8 / 8.1, 100^3 49 / 40; flat_block).
 template <int S, bool ODD, int ROUNDS, bool STATS, int GHOSTS, int BLOCK, bool NT>
 __global__ void __launch_bounds__(BLOCK) step_flat_kernel(const StepArgs a) {
   uint32_t tile = blockIdx.x;
@@ -405,7 +406,8 @@ __global__ void __launch_bounds__(kMaxRowWaves * 64) step_row_kernel(const StepA
 // graph of several steps (offsets 0, 1, ...) can be replayed from any t; the
 // parity is a template parameter, and the host only replays graphs of an even
 // number of steps from an even step count.  kGhostsEq: every replica has every
-// omega_g = 1; otherwise each replica's own setting is read at run time.
+// omega_g = 1; kGhostsRec: each replica's own setting, whichever it is, is read at
+// run time.
 // NT: non-temporal accesses on even steps (batch_even_nt, policy.hpp).
 // STATS: each tile's statistics are reduced in the block (fixed order, FP64)
 // into column t of b.partials, for batch_stats_reduce.
