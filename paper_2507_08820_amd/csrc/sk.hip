@@ -15,11 +15,11 @@
 //     transforms are not written again.
 // Reads and writes are of 8 bytes x 16 neighbouring columns; a block's lines fill
 // 32 KiB of LDS.  The floor is memory (256^3 FP32: 0.38 + 0.21 + 0.10 ms at copy
-// rate); measured 0.51 + 0.30 + 0.31 ms, the last two held by the LDS passes and
+// rate); measured 0.52 + 0.31 + 0.32 ms, the last two held by the LDS passes and
 // their index arithmetic.  A snapshot, against moment fields, one hipFFT
-// transform and one binning kernel per field (43 launches): 256^3 FP32 1.14 / 2.64
-// ms, 128^3 FP16 0.12 / 0.79, 64^3 0.031 / 0.22, 16^3 0.020 / 0.12, 200 x 320 x
-// 180 BF16 0.87 / 2.2.
+// transform and one binning kernel per field (43 launches): 256^3 FP32 1.06 / 2.62
+// ms, 128^3 FP16 0.12 / 0.78, 64^3 0.032 / 0.21, 16^3 0.021 / 0.11, 200 x 320 x
+// 180 BF16 0.78 / 2.16.
 // The other way stays for sides beyond 1024 (LDS), and where the sums of prime
 // factors above 7 cost more than hipFFT's transforms (sk_fits, policy.hpp).
 #include <hip/hip_runtime.h>

@@ -52,7 +52,7 @@ constexpr int kBlock = 256;
 // is a kernel of its own, for compiled into one with the first it cost BGK and
 // general rates 8 registers (85 -> 77, 5 -> 6 waves a SIMD: BGK 256^3 FP16 354 ->
 // 345 us a step, 128^3 FP16 41.9 -> 40.9, 130 x 50 x 70 BF16 12.6 -> 12.45).
-enum Ghosts : int { kGhostsProjected = 0, kGhostsEq = 1, kGhostsRec = 2 };
+enum Ghosts : int { kGhostsProjected = 0, kGhostsEq = 1, kGhostsRec = 2, kGhostsPerReplica = 2 };
 
 // Staged statistics, one LDS row per column: node `tid` at stat_at(tid).  The gap
 // after every 32 puts the values that the summing threads (8 parts of 32 nodes
@@ -406,8 +406,7 @@ __global__ void __launch_bounds__(kMaxRowWaves * 64) step_row_kernel(const StepA
 // graph of several steps (offsets 0, 1, ...) can be replayed from any t; the
 // parity is a template parameter, and the host only replays graphs of an even
 // number of steps from an even step count.  kGhostsEq: every replica has every
-// omega_g = 1; kGhostsRec: each replica's own setting, whichever it is, is read at
-// run time.
+// omega_g = 1; kGhostsPerReplica: each replica's own setting is read at run time.
 // NT: non-temporal accesses on even steps (batch_even_nt, policy.hpp).
 // STATS: each tile's statistics are reduced in the block (fixed order, FP64)
 // into column t of b.partials, for batch_stats_reduce.
@@ -822,7 +821,7 @@ hipError_t launch_batch_step(int storage, bool odd, int rounds, bool all_ghost_e
   if (all_ghost_eq) {                                                                          \
     RFLBM_BATCH_ST(S, O, R, kGhostsEq)                                                              \
   } else {                                                                                     \
-    RFLBM_BATCH_ST(S, O, R, kGhostsRec)                                                             \
+    RFLBM_BATCH_ST(S, O, R, kGhostsPerReplica)                                                             \
   }
 #define RFLBM_BATCH_R(S, O)                                                                    \
   switch (rounds) {                                                                            \
