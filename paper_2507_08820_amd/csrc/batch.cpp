@@ -291,7 +291,7 @@ rflbm_status time_batch(rflbm_batch* b, int64_t nsteps, double* ms) {
 
 // Raised with every change of the batch kernels or their order of tiles that can
 // change the fastest shape, so that a choice cached before is timed again.
-constexpr int kTuneRevision = 2;
+constexpr int kTuneRevision = 3;
 
 std::string batch_signature(const rflbm_batch* b) {
   // FNV-1a over the replica boxes; storage, rounds, ghosts (two kernels) and count spelled out

@@ -416,7 +416,7 @@ __global__ void __launch_bounds__(kBlock) batch_kernel(const BatchArgs b) {
   [[maybe_unused]] float (*stat_wave)[kMaxRowWaves] = nullptr;
   constexpr bool SMALL_BOX = true;  // every replica region is below 4 GiB
   constexpr bool BRICKS = false;    // replicas keep the plain layout
-  constexpr bool NOISE_FIRST = false;
+  constexpr bool NOISE_FIRST = S == kF32;
   // buffer instructions measured faster for 16-bit storage, global ones for
   // FP32 (64 replicas of 32^3..96^3: 38.9 vs 36.6 and 24.6 vs 25.9 GLUPS)
   constexpr bool BUFFER_ACCESS = S != kF32;
