@@ -15,7 +15,7 @@
 //     transforms are not written again.
 // Reads and writes are of 8 bytes x 16 neighbouring columns; a block's lines fill
 // 32 KiB of LDS.  The floor is memory (256^3 FP32: 0.38 + 0.21 + 0.10 ms at copy
-// rate); measured 0.52 + 0.31 + 0.32 ms, the last two held by the LDS passes and
+// rate); measured 0.51 + 0.31 + 0.30 ms, the last two held by the LDS passes and
 // their index arithmetic.  A snapshot, against moment fields, one hipFFT
 // transform and one binning kernel per field (43 launches): 256^3 FP32 1.06 / 2.62
 // ms, 128^3 FP16 0.12 / 0.78, 64^3 0.032 / 0.21, 16^3 0.021 / 0.11, 200 x 320 x
